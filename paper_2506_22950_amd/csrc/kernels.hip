@@ -75,15 +75,21 @@ hipError_t layers_resident(const KernelKey& key, int* resident) {
   return hipSuccess;
 }
 
+// Work-groups of a prefill over n units of work: one each, up to a grid the
+// kernels then stride over.
+static unsigned prefill_grid(int64_t n) { return (unsigned)(n < (1 << 20) ? n : (1 << 20)); }
+
 #define INFS_PREFILL_CASE(bf, d, mf, k8)                                                               \
   if (key.bf16 == bf && key.head_dim == d && key.mfma == mf && key.kv8 == (k8 ? 1 : 0)) {              \
     using SH = Shape<bf, d, 1, mf, mf ? 16 : 8, k8>;                                                   \
+    const int64_t rows = (int64_t)plen * hkv, blocks = (int64_t)hkv * ((plen + kMfmaBlock - 1) / kMfmaBlock); \
     if constexpr (mf)                                                                                  \
-      hipLaunchKernelGGL(prefill_mfma_kernel<SH>, dim3(grid), dim3(256), 0, stream, (char*)store,      \
+      hipLaunchKernelGGL(prefill_mfma_kernel<SH>, dim3(prefill_grid(blocks)), dim3(256), 0, stream, (char*)store, \
                          (const uint16_t*)k, (const uint16_t*)v, prompt, plen, hkv, pmax);             \
     else                                                                                               \
-      hipLaunchKernelGGL(prefill_plain_kernel<SH>, dim3(grid), dim3(256), 0, stream, (char*)store,     \
-                         (const char*)k, (const char*)v, prompt, plen, hkv, pmax);                     \
+      hipLaunchKernelGGL(prefill_plain_kernel<SH>,                                                     \
+                         dim3(prefill_grid((rows * SH::LPT + 256 * kPrefillUnits - 1) / (256 * kPrefillUnits)), 2), \
+                         dim3(256), 0, stream, (char*)store, (const char*)k, (const char*)v, prompt, plen, hkv, pmax); \
     return hipGetLastError();                                                                          \
   }
 
@@ -101,8 +107,6 @@ hipError_t launch_xcd_probe(int32_t* out, int blocks, hipStream_t stream) {
 hipError_t launch_prefill(const KernelKey& key, void* store, const void* k, const void* v, int prompt, int plen,
                           int hkv, int pmax, hipStream_t stream) {
   if (plen == 0) return hipSuccess;
-  const int64_t units = (int64_t)hkv * 2 * ((plen + 31) / 32) * 32 * key.head_dim;
-  const int grid = (int)((units / 8 + 255) / 256 < 4096 ? (units / 8 + 255) / 256 : 4096);
   INFS_PREFILL_CASE(false, 64, 0, false)
   INFS_PREFILL_CASE(false, 128, 0, false)
   INFS_PREFILL_CASE(true, 64, 0, false)
