@@ -352,7 +352,7 @@ infs_status infs_set_step_split(infs_ctx* ctx, int32_t mode);
    work-groups per KV head (infs_step_launch_workgroups / num_kv_heads), S slots of which slot s holds
    len[s] tokens (0 = idle), n_prefix_items prefix chunks of prefix_split tokens (a step launch in mode 1
    takes the prefix in chunks of 128 tokens on MFMA tiles, or of 256 where the
-   128-token ones would give some work-group two items, and of split_tokens on the wavefront path),
+   128-token ones would give some work-group two items, and of split_tokens on row tiles),
    response chunks of
    `split` tokens (split_tokens of the context, 256 for 0) and at most scmax of them per slot
    (ceil(max_suffix_len / split)).  Writes pieces[0..S) (response items per slot) and roles[0..5) =
@@ -371,8 +371,9 @@ infs_status infs_get_stats(const infs_ctx* ctx, infs_stats* out);
 
 /* The decode kernel instantiation a context runs, fixed by infs_create from the element type, head
    size, heads per KV head and m * hpk prefix rows: bf16 (0: fp32 Q/K/V, 1: bf16), head_dim, hpk,
-   mfma (1: the prefix contractions run on 16x16x32 MFMA tiles, 0: on wavefront dot products),
-   prefix_rows (the row tile, padded: 8/16 on the wavefront path, 16/32/64/128 on MFMA tiles),
+   mfma (1: the prefix is stored in 32-token blocks of 16x16x32 MFMA operands, chunks of 128 tokens; 0: as
+   plain rows, read by one row tile per wavefront, chunks of split_tokens), prefix_rows (the row tile,
+   padded: 8/16 over plain rows, 16/32/64/128 over MFMA blocks),
    kv_fp8 (1: K/V stored as E4M3).  probe_* describe the kernel of infs_probe_step launches
    (probe_prefix_rows = 0 without a probe phase).  For diagnostics and tests; dry-run contexts
    answer too. */

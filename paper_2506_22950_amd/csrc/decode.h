@@ -8,9 +8,10 @@
 //     and used by all m * hpk query rows of that
 //     KV head -- the rows of every live slot of the prompt.  With >= 16 rows
 //     the two contractions run on MFMA tiles (v_mfma_f32_16x16x32_bf16);
-//     below that, on wavefront dot products;
+//     below that, and in fp32, on one 16-row tile per wavefront over plain rows;
 //   * split-K attention over each live slot's private response (hpk rows per
-//     KV byte, wavefront dot products);
+//     KV byte): MFMA tiles for bf16 and E4M3 pages, row tiles or wavefront dot
+//     products for fp32 pages;
 //   * log-sum-exp merge: one work-group per live (slot, KV head), placed at
 //     the end of the grid, waits (bounded) until every chunk of that slot has
 //     published its partial, combines the partial softmaxes and writes O.
@@ -101,17 +102,9 @@ __device__ __forceinline__ float dot16B(const u32x4& k, const u32x4& q) {
   }
 }
 
-template <bool BF>
 __device__ __forceinline__ void axpy16B(float* o, float p, const u32x4& v) {
-  if constexpr (BF) {
-    o[0] = fmaf(p, bf_lo(v.x), o[0]); o[1] = fmaf(p, bf_hi(v.x), o[1]);
-    o[2] = fmaf(p, bf_lo(v.y), o[2]); o[3] = fmaf(p, bf_hi(v.y), o[3]);
-    o[4] = fmaf(p, bf_lo(v.z), o[4]); o[5] = fmaf(p, bf_hi(v.z), o[5]);
-    o[6] = fmaf(p, bf_lo(v.w), o[6]); o[7] = fmaf(p, bf_hi(v.w), o[7]);
-  } else {
-    o[0] = fmaf(p, __uint_as_float(v.x), o[0]); o[1] = fmaf(p, __uint_as_float(v.y), o[1]);
-    o[2] = fmaf(p, __uint_as_float(v.z), o[2]); o[3] = fmaf(p, __uint_as_float(v.w), o[3]);
-  }
+  o[0] = fmaf(p, __uint_as_float(v.x), o[0]); o[1] = fmaf(p, __uint_as_float(v.y), o[1]);
+  o[2] = fmaf(p, __uint_as_float(v.z), o[2]); o[3] = fmaf(p, __uint_as_float(v.w), o[3]);
 }
 
 // Compile-time shape of one kernel instantiation.
@@ -128,7 +121,7 @@ struct Shape {
   static constexpr int ES = BF ? 2 : 4;            // element bytes
   static constexpr int EPL = 16 / ES;              // elements per lane chunk
   static constexpr int ROWB = D * ES;              // bytes of one K or V row of one head
-  static constexpr int LPT = ROWB / 16;            // lanes per token (wavefront path)
+  static constexpr int LPT = ROWB / 16;            // lanes per token (16-byte units of a row)
   static constexpr int TPI = 64 / LPT;             // tokens per load instruction
   static constexpr int KES = KV8 ? 1 : ES;        // bytes per stored K/V element
   static constexpr int KROWB = D * KES;            // bytes of one stored K or V row of one head
@@ -146,14 +139,17 @@ struct Shape {
   static constexpr int TG = kWaves / RG;
   static constexpr int BPW = (kMfmaPrefixSplit / kMfmaBlock) / TG;
   static constexpr int WAVE_NR = (!MFMA && PR > HPK) ? PR : HPK;
-  static constexpr int WAVE_SMEM = 4 * WAVE_NR * (D + 2);
+  static constexpr int WAVE_SMEM = 4 * WAVE_NR * (D + 6);  // see RowTile::SMEM
+  // fp32 responses of 4 or 8 rows run on row tiles.  A tile costs the same for
+  // any row count, the wavefront dot products cost by the row: with 2 rows a
+  // small group's step (d = 64) takes 8.3 us with them and 10.8 us with tiles, a
+  // four-layer group decode (P = 1328) 42.2 and 47.1 ms.
+  static constexpr bool RESP_ROWS = !BF && HPK >= 4;
   static constexpr int MFMA_SLOT = (MFMA && TG > 1) ? (NBW * DB * 64 * 4 + 2 * NBW * 64) : 0;
   static constexpr int MFMA_SMEM = kWaves * MFMA_SLOT;
   static constexpr int SMEM = WAVE_SMEM > MFMA_SMEM ? WAVE_SMEM : MFMA_SMEM;
-  // 16 wavefront rows keep as many accumulators live as fill a SIMD's
-  // registers at two wavefronts: that shape runs one per SIMD rather than
-  // spill; every other shape runs (at least) two per SIMD.
-  static constexpr int MIN_WAVES = (!MFMA && PR >= 16) ? 1 : 2;
+  // wavefronts per SIMD the kernels are compiled for
+  static constexpr int MIN_WAVES = 2;
   static_assert(LPT >= 2 && LPT <= 64, "row size");
   static_assert(!MFMA || BF, "MFMA path is bf16");
   static_assert(!KV8 || (BF && MFMA), "FP8 KV on the bf16 MFMA shapes");
@@ -287,7 +283,7 @@ __device__ __forceinline__ float wave_sum(float x) {
 }
 
 // ----------------------------------------------------------------------------
-// Wavefront path: NR query rows over the token range [t0, t1) of one KV head.
+// Wavefront dot products: NR query rows over the token range [t0, t1) of one KV head.
 // LPT consecutive lanes hold one token's row (16 B each), so a load
 // instruction covers TPI tokens; U loads per lane for K and for V are issued
 // together before any arithmetic.  Each token group keeps its own running
@@ -365,30 +361,11 @@ __device__ __forceinline__ void wave_partial(const Addr& ad, int t0, int t1, con
         l[r] *= corr;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) o[r][e] *= corr;
-        if constexpr (SH::BF) {
-          // P.V two tokens at a time with bf16 dot products: the probabilities
-          // are rounded to bf16 and the normaliser sums the same rounded values.
 #pragma unroll
-          for (int x = 0; x < SB; x += 2) {
-            const int u = b * SB + x;
-            const __bf16 h0 = (__bf16)exp2_fast(s[x][r] - mu), h1 = (__bf16)exp2_fast(s[x + 1][r] - mu);
-            l[r] += (float)h0 + (float)h1;
-            const bf16x2 pb = {h0, h1};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const uint32_t lo = __builtin_amdgcn_perm(vv[u + 1][k], vv[u][k], 0x05040100u);  // elems 2k
-              const uint32_t hi = __builtin_amdgcn_perm(vv[u + 1][k], vv[u][k], 0x07060302u);  // elems 2k+1
-              o[r][2 * k] = __builtin_amdgcn_fdot2_f32_bf16(pb, __builtin_bit_cast(bf16x2, lo), o[r][2 * k], false);
-              o[r][2 * k + 1] = __builtin_amdgcn_fdot2_f32_bf16(pb, __builtin_bit_cast(bf16x2, hi), o[r][2 * k + 1], false);
-            }
-          }
-        } else {
-#pragma unroll
-          for (int x = 0; x < SB; ++x) {
-            const float p = exp2_fast(s[x][r] - mu);
-            l[r] += p;
-            axpy16B<false>(o[r], p, vv[b * SB + x]);
-          }
+        for (int x = 0; x < SB; ++x) {
+          const float p = exp2_fast(s[x][r] - mu);
+          l[r] += p;
+          axpy16B(o[r], p, vv[b * SB + x]);
         }
       }
     }
@@ -412,7 +389,7 @@ __device__ __forceinline__ void fold_token(const u32x4& k, const u32x4& v, const
       l[r] = l[r] * corr + p;
 #pragma unroll
       for (int e = 0; e < SH::EPL; ++e) o[r][e] *= corr;
-      axpy16B<SH::BF>(o[r], p, v);
+      axpy16B(o[r], p, v);
     }
   }
 }
@@ -490,21 +467,6 @@ __device__ __forceinline__ void combine_store_partial(float* smem, const Exchang
     if (d == 0) ex.store_ml(rec0 + r, M, L);
   }
 }
-
-// Addressing of the plain prefix store: [prompt][kv][K|V][max_prompt_len][D].
-// Row of token tokbase + (lane / LPT), clamped below `end` so that masked
-// tokens still read inside this head's region.
-template <class SH>
-struct PrefixAddr {
-  static constexpr bool kNonTemporal = false;
-  const char* base[2];
-  __device__ int page(int) const { return 0; }
-  __device__ const char* row(int kind, int tokbase, int, int, int end) const {
-    const int lane = threadIdx.x & 63;
-    const int tok = min(tokbase + lane / SH::LPT, end - 1);
-    return base[kind] + (int64_t)tok * SH::KROWB + (lane % SH::LPT) * SH::LANEB;
-  }
-};
 
 // Addressing of a slot's stored response tokens: pages [page][kv][K|V][16][D].
 // Lane i of `pages` holds the page of the wave's i-th 16-token group.  A load
@@ -773,38 +735,329 @@ struct RespMfma {
   }
 };
 
+// ----------------------------------------------------------------------------
+// Row tile: up to 16 query rows over tokens whose K and V are stored as plain
+// rows (the prefix store below 16 MFMA rows or in fp32, and fp32 pages).  One
+// wavefront, S^T[tok][row] = K[tok] . Q[row] and O^T[d][row] += V^T[d][tok]
+// P^T[tok][row] on 16x16 matrix tiles: fp32 on v_mfma_f32_16x16x4_f32 (fp32
+// products and sums), bf16 on v_mfma_f32_16x16x32_bf16.  row = lane % 16 on
+// S^T, O^T and the running (m, l), h = lane / 16 below.
+//   K operand: 16 bytes at chunk 4kb + h of token lane % 16 -- an element e of
+//     it belongs to dim (4kb + h) * EPL + e, and the query operand holds the
+//     same, so the order of the contraction does not matter.
+//   V operand: token 4h + r (r = 0..3, what a lane's scores of a 16-token tile
+//     are), VB bytes at chunk c = 16nv + lane % 16.  Element e of the chunk is
+//     one output tile: its row i is dim (16nv + i) * VE + e.  fp32 takes the
+//     lane's element as it is (one k-step per r); bf16 packs the eight tokens of
+//     a 32-token group (16mb + 4h + r) per element with v_perm.
+// Every load is 16 bytes a lane (8 for bf16 rows of 64) of whole 64-byte pieces
+// of rows.  Bound by the matrix unit in fp32 (2048 cycles per 16 tokens and 16
+// rows at d = 128), by loads in bf16.  The wavefront dot products it replaces
+// spent their time summing across lanes: a 28-layer fp32 step of 8 slots (2
+// rows each, 16 prefix rows, P = 1000) took 1834 us with them at one wavefront
+// per SIMD and takes 496 us with tiles at two; bf16 with 2 rows (8 layers,
+// P = 2483) took 213 us and takes 151.  Short chains keep the fp32 error where
+// it was (1.8e-7 against 1.9e-7 relative); one chain of D is 465 us and 2.1e-7.
+// ----------------------------------------------------------------------------
+template <class SH, int NR>
+struct RowTile {
+  static constexpr bool BF = SH::BF;
+  static constexpr int D = SH::D, EPL = SH::EPL, KB = SH::LPT / 4;
+  static constexpr int GT = BF ? 32 : 16, MBS = GT / 16;                 // tokens and 16-token tiles of a group
+  static constexpr int VB = SH::ROWB >= 256 ? 16 : 8, VE = VB / SH::ES;  // V bytes / elements of a lane's load
+  static constexpr int NV = SH::ROWB / (16 * VB);
+  static constexpr int NT = D / 16;                                      // output tiles: nv * VE + e
+  static constexpr int NG = 128 / (GT * SH::ROWB * 2 / 256);             // groups per load round: 128 registers
+  static constexpr int TOK = NG * GT;
+  static constexpr int PITCH = D + 4;                 // LDS floats per published row: rows on different banks
+  static constexpr int SMEM = kWaves * NR * (PITCH + 2);
+  static_assert(NR <= 16 && NV * VE == NT && KB >= 1 && NG >= 1, "tile shape");
+  using VReg = std::conditional_t<VB == 16, u32x4, u32x2>;
+  struct Regs {
+    u32x4 k[NG][MBS][KB];
+    VReg v[NG][MBS][4][NV];
+  };
+  static constexpr int kLoads = NG * MBS * (KB + 4 * NV);
+  struct Acc {
+    f32x4 o[NT];
+    float m, l;  // l: this lane's share of the row's sum
+  };
+
+  // Loads of tokens base .. base + TOK - 1; ad.row(kind, t16, off) is the row of
+  // token t16 + off (t16 a uniform multiple of 16, off < 16), any readable row
+  // past the range's end.
+  template <class Addr>
+  __device__ __forceinline__ static void load_round(const Addr& ad, int base, Regs& R) {
+    const int lane = threadIdx.x & 63, i = lane & 15, h = lane >> 4;
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int mb = 0; mb < MBS; ++mb) {
+        const char* kr = ad.row(0, base + g * GT + mb * 16, i) + h * 16;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) R.k[g][mb][kb] = Addr::template load<u32x4>(kr + kb * 64);
+      }
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int mb = 0; mb < MBS; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const char* vr = ad.row(1, base + g * GT + mb * 16, 4 * h + r) + i * VB;
+#pragma unroll
+          for (int nv = 0; nv < NV; ++nv) R.v[g][mb][r][nv] = Addr::template load<VReg>(vr + nv * 16 * VB);
+        }
+  }
+
+  // Query operand from row pointer qr of this lane's row (null: a zero row).
+  __device__ __forceinline__ static void load_q(const char* qr, u32x4 (&q)[KB]) {
+    const int h = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) q[kb] = qr ? *(const u32x4*)(qr + (4 * kb + h) * 16) : u32x4{0, 0, 0, 0};
+  }
+
+  __device__ __forceinline__ static void init(Acc& A) {
+    A.m = NEG_INF;
+    A.l = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) A.o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  // A partial that holds one token, given by its rows (fp32 pages: the newest token).
+  __device__ __forceinline__ static void start_row(const char* krow, const char* vrow, const u32x4 (&q)[KB], float sl2,
+                                                   Acc& A) {
+    static_assert(!BF, "fp32 rows");
+    const int h = (threadIdx.x & 63) >> 4;
+    float s = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) s += dot16B<false>(*(const u32x4*)(krow + (4 * kb + h) * 16), q[kb]);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    A.m = s * sl2;
+    A.l = h == 0 ? 1.f : 0.f;
+#pragma unroll
+    for (int nv = 0; nv < NV; ++nv)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const f32x4 x = *(const f32x4*)(vrow + (nv * 16 + 4 * h + r) * VB);
+#pragma unroll
+        for (int e = 0; e < VE; ++e) A.o[nv * VE + e][r] = x[e];
+      }
+  }
+
+  // Tokens base .. base + TOK - 1 (the round held in R), of which those below t1
+  // count: one online-softmax step per group.
+  __device__ __forceinline__ static void round(Regs& R, const u32x4 (&q)[KB], int base, int t1, float sl2, Acc& A) {
+    const int h = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const int gb = base + g * GT;
+      if (gb >= t1) break;
+      f32x4 st[MBS];
+#pragma unroll
+      for (int mb = 0; mb < MBS; ++mb) {
+        // short chains of products, added pairwise: sums of few terms round less than
+        // one of D, and no product waits for the last
+        constexpr int NC = BF ? KB : 2 * KB;
+        f32x4 t[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          t[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (BF) {
+            t[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, R.k[g][mb][c]),
+                                                           __builtin_bit_cast(bf16x8, q[c]), t[c], 0, 0, 0);
+          } else {
+#pragma unroll
+            for (int e = 2 * (c & 1); e < 2 * (c & 1) + 2; ++e)
+              t[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(R.k[g][mb][c / 2][e]),
+                                                          __uint_as_float(q[c / 2][e]), t[c], 0, 0, 0);
+          }
+#pragma unroll
+          for (int n = 1; (c + 1) % (2 * n) == 0; n *= 2) t[c + 1 - 2 * n] += t[c + 1 - n];
+        }
+        st[mb] = t[0] * sl2;
+      }
+      if (gb + GT > t1) {  // the range ends inside: mask scores, clear V (0 * whatever is there must be 0)
+#pragma unroll
+        for (int mb = 0; mb < MBS; ++mb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const bool in = gb + mb * 16 + 4 * h + r < t1;
+            st[mb][r] = in ? st[mb][r] : NEG_INF;
+#pragma unroll
+            for (int nv = 0; nv < NV; ++nv) R.v[g][mb][r][nv] = in ? R.v[g][mb][r][nv] : VReg{};
+          }
+      }
+      float mx = fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3]));
+      if constexpr (MBS == 2) mx = fmaxf(mx, fmaxf(fmaxf(st[1][0], st[1][1]), fmaxf(st[1][2], st[1][3])));
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float mn = fmaxf(A.m, mx);
+      const float mu = (mn == NEG_INF) ? 0.f : mn;
+      const float corr = exp2_fast(A.m - mu);
+      A.m = mn;
+      if constexpr (BF) {
+        // A probability is weighed as the sum of two bf16 numbers (its rounding and
+        // what that leaves), so it keeps 16 bits of mantissa on bf16 products.
+        bf16x8 ph, pl;
+        A.l *= corr;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) A.o[t] *= corr;
+#pragma unroll
+        for (int mb = 0; mb < MBS; ++mb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float x = exp2_fast(st[mb][r] - mu);
+            ph[mb * 4 + r] = (__bf16)x;
+            pl[mb * 4 + r] = (__bf16)(x - (float)(__bf16)x);
+            A.l += x;
+          }
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+          const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+          u32x4 a;
+#pragma unroll
+          for (int y = 0; y < 4; ++y)  // tokens (16mb + 4h) + 2(y%2), +1 with mb = y/2
+            a[y] = __builtin_amdgcn_perm(R.v[g][y / 2][2 * (y & 1) + 1][0][e / 2], R.v[g][y / 2][2 * (y & 1)][0][e / 2], sel);
+          A.o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), pl, A.o[e], 0, 0, 0);
+          A.o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), ph, A.o[e], 0, 0, 0);
+        }
+      } else {
+        // the group's sum starts from zero and joins the running one as a whole:
+        // short chains, as for the scores
+        float x[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = exp2_fast(st[0][r] - mu);
+        A.l = A.l * corr + ((x[0] + x[1]) + (x[2] + x[3]));
+#pragma unroll
+        for (int nv = 0; nv < NV; ++nv)
+#pragma unroll
+          for (int e = 0; e < VE; ++e) {
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(R.v[g][0][r][nv][e]), x[r], c, 0, 0, 0);
+            A.o[nv * VE + e] = A.o[nv * VE + e] * corr + c;
+          }
+      }
+    }
+  }
+
+  // Combine the four wavefronts' partials through LDS and store rows [0, NR) at
+  // records rec0 + row.
+  template <bool L2>
+  __device__ __forceinline__ static void store(float* smem, Acc& A, const Exchange<L2>& ex, int64_t rec0) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, row = lane & 15, h = lane >> 4;
+    float* sml = smem + kWaves * NR * PITCH;
+    A.l += __shfl_xor(A.l, 16);
+    A.l += __shfl_xor(A.l, 32);
+    if (row < NR) {
+      float* so = smem + (w * NR + row) * PITCH;
+#pragma unroll
+      for (int nv = 0; nv < NV; ++nv)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int e = 0; e < VE; e += 4)  // dims (16nv + 4h + r) * VE + e .. + 3
+            *(f32x4*)(so + (nv * 16 + 4 * h + r) * VE + e) =
+                f32x4{A.o[nv * VE + e][r], A.o[nv * VE + e + 1][r], A.o[nv * VE + e + 2][r], A.o[nv * VE + e + 3][r]};
+      if (h == 0) {
+        sml[(w * NR + row) * 2 + 0] = A.m;
+        sml[(w * NR + row) * 2 + 1] = A.l;
+      }
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < NR * (D / 4); x += kBlockThreads) {
+      const int r = x / (D / 4), d = (x - r * (D / 4)) * 4;
+      float M = NEG_INF;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) M = fmaxf(M, sml[(v * NR + r) * 2]);
+      const float Mu = (M == NEG_INF) ? 0.f : M;
+      float L = 0.f;
+      f32x4 O = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {
+        const float wgt = exp2_fast(sml[(v * NR + r) * 2] - Mu);
+        L += wgt * sml[(v * NR + r) * 2 + 1];
+        O += *(const f32x4*)(smem + (v * NR + r) * PITCH + d) * wgt;
+      }
+      ex.store4((uint32_t)(((rec0 + r) * D + d) * 4), O);
+      if (d == 0) ex.store_ml(rec0 + r, M, L);
+    }
+  }
+};
+
+// Rows of the plain prefix store: [prompt][kv][K|V][max_prompt_len][D].  Tokens
+// past `end` read its last row (masked by the tile), inside this head's region.
+template <class SH>
+struct PrefixRows {
+  const char* base[2];
+  int end;
+  __device__ PrefixRows(const StepArgs& a, const char* prefix, int p, int g, int end_) : end(end_) {
+    const int64_t head = ((int64_t)p * a.Hkv + g) * 2;
+    base[0] = prefix + head * a.max_prompt_len * SH::KROWB;
+    base[1] = prefix + (head + 1) * a.max_prompt_len * SH::KROWB;
+  }
+  __device__ const char* row(int kind, int t16, int off) const {
+    return base[kind] + (int64_t)min(t16 + off, end - 1) * SH::KROWB;
+  }
+  template <class T>
+  __device__ static T load(const char* p) {
+    return *(const T*)p;
+  }
+};
+// Rows of a response in fp32 pages [page][kv][K|V][16][D]; lane i of `pages`
+// holds the page of the wavefront's i-th 16-token group (entries past its range
+// name page 0).  Non-temporal, as all response K/V.
+template <class SH>
+struct PageRows {
+  const char* pool;
+  int pages, hkv, g, first;  // first: the wavefront's first token
+  __device__ const char* row(int kind, int t16, int off) const {
+    const int pg = __builtin_amdgcn_readlane(pages, min((t16 - first) >> 4, 63));
+    return pool + ((int64_t)(pg * hkv + g) * 2 + kind) * SH::PAGEB + off * SH::KROWB;
+  }
+  template <class T>
+  __device__ static T load(const char* p) {
+    return __builtin_nontemporal_load((const T*)p);
+  }
+};
+
 __device__ __forceinline__ int64_t prefix_records(const StepArgs& a, int pr) {
   return (int64_t)a.num_prompts * a.prefix_chunks_max * a.Hkv * pr;
 }
 
 // ----------------------------------------------------------------------------
-// Prefix chunk, wavefront path (fewer than 16 rows): rows r = slot_in_prompt * hpk + j.
+// Prefix chunk on row tiles (fp32, or fewer than 16 rows): rows r =
+// slot_in_prompt * hpk + j, a quarter of the chunk's tokens per wavefront.
 // ----------------------------------------------------------------------------
+// This lane's query row of prefix work item (prompt p, KV head g): null for
+// padding rows and rows of idle slots.
+template <class SH>
+__device__ __forceinline__ const char* prefix_query(const StepArgs& a, const void* q, int p, int g) {
+  const int r = threadIdx.x & 15, si = r / SH::HPK, j = r - si * SH::HPK, s = p * a.m + min(si, a.m - 1);
+  return r < a.prefix_rows && a.slot[s].len > 0 ? (const char*)q + ((int64_t)s * a.Hq + g * SH::HPK + j) * SH::ROWB
+                                                : nullptr;
+}
+
 template <class SH, bool L2>
-__device__ void prefix_wave(const StepArgs& a, int p, int c, int g, float* smem) {
-  constexpr int PR = SH::PR, HPK = SH::HPK;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, ch = lane % SH::LPT;
-  const int plen = a.prompt[p].plen;
-  const int t0 = c * a.prefix_split, t1 = min(t0 + a.prefix_split, plen);
-  const int sub = a.prefix_split / 4;
+__device__ void prefix_rows(const StepArgs& a, int p, int c, int g, float* smem) {
+  using T = RowTile<SH, SH::PR>;
+  const int w = threadIdx.x >> 6;
+  const int t0 = c * a.prefix_split, t1 = min(t0 + a.prefix_split, a.prompt[p].plen), sub = a.prefix_split / kWaves;
   const int wt0 = min(t0 + w * sub, t1), wt1 = min(wt0 + sub, t1);
-  u32x4 q[PR];
-#pragma unroll
-  for (int r = 0; r < PR; ++r) {
-    const int si = r / HPK, j = r - si * HPK, s = p * a.m + min(si, a.m - 1);
-    if (r < a.prefix_rows && a.slot[s].len > 0)
-      q[r] = *((const u32x4*)((const char*)a.q + ((int64_t)s * a.Hq + g * HPK + j) * SH::ROWB) + ch);
-    else
-      q[r] = u32x4{0, 0, 0, 0};
+  const PrefixRows<SH> ad(a, (const char*)a.prefix, p, g, wt1);
+  typename T::Regs R;
+  T::load_round(ad, wt0, R);
+  u32x4 q[T::KB];
+  T::load_q(prefix_query<SH>(a, a.q, p, g), q);
+  typename T::Acc A;
+  T::init(A);
+  for (int base = wt0; base < wt1; base += T::TOK) {
+    if (base != wt0) T::load_round(ad, base, R);
+    T::round(R, q, base, wt1, a.scale_log2, A);
   }
-  const int64_t head = ((int64_t)p * a.Hkv + g) * 2;
-  PrefixAddr<SH> ad{{(const char*)a.prefix + head * a.max_prompt_len * SH::KROWB,
-                     (const char*)a.prefix + (head + 1) * a.max_prompt_len * SH::KROWB}};
-  float m[PR], l[PR], o[PR][SH::EPL];
-  wave_partial<SH, PR>(ad, wt0, wt1, q, a.scale_log2, m, l, o);
-  wave_combine_groups<SH, PR>(m, l, o);
-  const int64_t rec0 = (((int64_t)p * a.Hkv + g) * a.prefix_chunks_max + c) * PR;
-  block_store_partial<SH, PR, L2>(smem, m, l, o, Exchange<L2>(a), rec0);
+  T::template store<L2>(smem, A, Exchange<L2>(a), (((int64_t)p * a.Hkv + g) * a.prefix_chunks_max + c) * SH::PR);
 }
 
 // ----------------------------------------------------------------------------
@@ -1015,13 +1268,29 @@ __device__ void prefix_mfma(const StepArgs& a, int p, int c, int g, float* smem)
 // Response chunk of one live slot (hpk rows), plus the append of this step's
 // K/V when the chunk holds the newest position.
 // ----------------------------------------------------------------------------
+// One wavefront copies the newest token's fp32 K and V rows into its page row.
+template <class SH>
+__device__ __forceinline__ void store_row(char* page_row, const char* krow, const char* vrow) {
+  const int lane = threadIdx.x & 63;
+  for (int x = lane; x < 2 * SH::LPT; x += 64) {
+    const int kind = x / SH::LPT, ch = x - kind * SH::LPT;
+    *(u32x4*)(page_row + kind * SH::PAGEB + ch * 16) = *(const u32x4*)((kind ? vrow : krow) + ch * 16);
+  }
+}
+
 template <class SH, bool L2>
 __device__ void suffix_chunk_mfma(const StepArgs& a, int s, int c, int g, float* smem);
+template <class SH, bool L2>
+__device__ void suffix_chunk_rows(const StepArgs& a, int s, int c, int g, float* smem);
 
 template <class SH, bool L2>
 __device__ void suffix_chunk(const StepArgs& a, int s, int c, int g, float* smem) {
   if constexpr (SH::BF) {
     suffix_chunk_mfma<SH, L2>(a, s, c, g, smem);
+    return;
+  }
+  if constexpr (SH::RESP_ROWS) {
+    suffix_chunk_rows<SH, L2>(a, s, c, g, smem);
     return;
   }
   constexpr int HPK = SH::HPK;
@@ -1050,10 +1319,6 @@ __device__ void suffix_chunk(const StepArgs& a, int s, int c, int g, float* smem
   if (has_new) {
     knew = *((const u32x4*)((const char*)a.knew + newrow) + ch);
     vnew = *((const u32x4*)((const char*)a.vnew + newrow) + ch);
-    if constexpr (SH::KV8) {  // attend to the token as the cache stores it
-      knew = widen_e4m3(narrow_e4m3(knew));
-      vnew = widen_e4m3(narrow_e4m3(vnew));
-    }
   }
   SuffixAddr<SH> ad{(const char*)a.pool, pages, a.Hkv, g};
   float m[HPK], l[HPK], o[HPK][SH::EPL];
@@ -1130,6 +1395,50 @@ __device__ void suffix_chunk_mfma(const StepArgs& a, int s, int c, int g, float*
   if (t1 == len && g == 0 && threadIdx.x == 0) {  // bookkeeping of this step's token (K/V stored above)
     const int pos = len - 1;
     a.page_table[(int64_t)sp.seq * a.pages_per_slot + (pos >> 4)] = sp.cur_page;
+    if (a.count_tokens)
+      __hip_atomic_fetch_add(&a.tokens[(s / a.m) * a.G + sp.sample], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// fp32 response chunk on a row tile: the wavefront whose range holds the newest
+// position starts from that token's rows and stores them into its page.
+template <class SH, bool L2>
+__device__ void suffix_chunk_rows(const StepArgs& a, int s, int c, int g, float* smem) {
+  using T = RowTile<SH, SH::HPK>;
+  constexpr int HPK = SH::HPK;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const SlotPlan& sp = a.slot[s];
+  const int len = sp.len, last = len - 1;
+  const int t0 = c * a.split, t1 = min(t0 + a.split, len), sub = a.split / kWaves;
+  const int wt0 = min(t0 + w * sub, t1), wt1 = min(wt0 + sub, t1);
+  const int npg = (wt1 - wt0 + kPageTokens - 1) / kPageTokens;
+  const int32_t* ptab = a.page_table + (int64_t)sp.seq * a.pages_per_slot + (wt0 >> 4);
+  const PageRows<SH> ad{(const char*)a.pool, lane < npg ? ptab[lane] : 0, a.Hkv, g, wt0};
+  const bool has_new = last >= wt0 && last < wt1;
+  const int te = has_new ? last : wt1;  // stored tokens of this wavefront: [wt0, te)
+  typename T::Regs R;
+  T::load_round(ad, wt0, R);
+  u32x4 q[T::KB];
+  const int row = lane & 15;
+  T::load_q(row < HPK ? (const char*)a.q + ((int64_t)s * a.Hq + g * HPK + row) * SH::ROWB : nullptr, q);
+  typename T::Acc A;
+  if (has_new) {
+    const int64_t newrow = ((int64_t)s * a.Hkv + g) * SH::ROWB;
+    T::start_row((const char*)a.knew + newrow, (const char*)a.vnew + newrow, q, a.scale_log2, A);
+    store_row<SH>((char*)a.pool + (int64_t)(sp.cur_page * a.Hkv + g) * 2 * SH::PAGEB + (last & 15) * SH::KROWB,
+                  (const char*)a.knew + newrow, (const char*)a.vnew + newrow);
+  } else {
+    T::init(A);
+  }
+  for (int base = wt0; base < te; base += T::TOK) {
+    if (base != wt0) T::load_round(ad, base, R);
+    T::round(R, q, base, te, a.scale_log2, A);
+  }
+  T::template store<L2>(smem, A, Exchange<L2>(a),
+                        prefix_records(a, SH::PR) + (((int64_t)s * a.Hkv + g) * a.suffix_chunks_max + c) * HPK);
+
+  if (t1 == len && g == 0 && threadIdx.x == 0) {  // bookkeeping of this step's token (K/V stored above)
+    a.page_table[(int64_t)sp.seq * a.pages_per_slot + (last >> 4)] = sp.cur_page;
     if (a.count_tokens)
       __hip_atomic_fetch_add(&a.tokens[(s / a.m) * a.G + sp.sample], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -1306,7 +1615,7 @@ __device__ __forceinline__ void decode_block(const StepArgs& a, float* smem, uns
     if constexpr (SH::MFMA)
       prefix_mfma<SH, L2>(a, p, c, g, smem);
     else
-      prefix_wave<SH, L2>(a, p, c, g, smem);
+      prefix_rows<SH, L2>(a, p, c, g, smem);
     arrive(a, p * a.m, a.m, g);
     return;
   }

@@ -1,4 +1,4 @@
-// Decode kernel instantiations: bf16 with fewer than 16 prefix rows, head_dim 128, wavefront reductions; 1/2/4/8 query heads per KV head, 8 or 16 padded rows.
+// Decode kernel instantiations: bf16 with fewer than 16 prefix rows, head_dim 128, prefix as plain rows on row tiles; 1/2/4/8 query heads per KV head, 8 or 16 padded rows.
 #include "layers.h"
 
 namespace infs {

@@ -12,7 +12,7 @@ struct KernelKey {
   int bf16;        // 0: fp32 Q/K/V, 1: bf16
   int head_dim;    // 64 or 128
   int hpk;         // query heads per KV head
-  int mfma;        // 1: prefix rows go through MFMA tiles, 0: wavefront reductions
+  int mfma;        // 1: prefix rows go through MFMA tiles, 0: row tiles over plain rows
   int prefix_rows; // rows of one prompt's prefix work item, padded (wave: 8/16; MFMA: 16/32/64/128)
   int kv8;         // 1: K/V stored as E4M3 (bf16 MFMA shapes of head_dim 128)
 };
@@ -21,8 +21,8 @@ struct KernelKey {
 // instantiation exists.
 bool select_kernel(int bf16, int head_dim, int hpk, int prefix_rows_real, int kv8, KernelKey* key);
 
-// The same with the prefix path fixed (mfma 1: MFMA tiles, 0: wavefront
-// reductions): a second kernel of a context must read the prefix store in the
+// The same with the prefix path fixed (mfma 1: MFMA tiles, 0: row
+// tiles over plain rows): a second kernel of a context must read the prefix store in the
 // layout its first kernel chose.
 bool select_kernel_path(int bf16, int head_dim, int hpk, int prefix_rows_real, int mfma, int kv8, KernelKey* key);
 
@@ -54,7 +54,7 @@ struct KernelTable {
   const KernelEntry* entries;
   int count;
 };
-KernelTable kernels_wave_f32_d64();    // fp32, head_dim 64 (wavefront reductions)
+KernelTable kernels_wave_f32_d64();    // fp32, head_dim 64
 KernelTable kernels_wave_f32_d128();   // fp32, head_dim 128
 KernelTable kernels_wave_bf16_d64();   // bf16 below 16 prefix rows, head_dim 64
 KernelTable kernels_wave_bf16_d128();  // bf16 below 16 prefix rows, head_dim 128

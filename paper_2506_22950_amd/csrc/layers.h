@@ -218,47 +218,14 @@ __device__ __forceinline__ void wave_compute(const Addr& ad, int t0, int t1, con
         l[r] *= corr;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) o[r][e] *= corr;
-        if constexpr (SH::BF) {
 #pragma unroll
-          for (int x = 0; x < SB; x += 2) {
-            const int u = b * SB + x;
-            const __bf16 h0 = (__bf16)exp2_fast(s[x][r] - mu), h1 = (__bf16)exp2_fast(s[x + 1][r] - mu);
-            l[r] += (float)h0 + (float)h1;
-            const bf16x2 pb = {h0, h1};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const uint32_t lo = __builtin_amdgcn_perm(R.vv[u + 1][k], R.vv[u][k], 0x05040100u);
-              const uint32_t hi = __builtin_amdgcn_perm(R.vv[u + 1][k], R.vv[u][k], 0x07060302u);
-              o[r][2 * k] = __builtin_amdgcn_fdot2_f32_bf16(pb, __builtin_bit_cast(bf16x2, lo), o[r][2 * k], false);
-              o[r][2 * k + 1] = __builtin_amdgcn_fdot2_f32_bf16(pb, __builtin_bit_cast(bf16x2, hi), o[r][2 * k + 1], false);
-            }
-          }
-        } else {
-#pragma unroll
-          for (int x = 0; x < SB; ++x) {
-            const float p = exp2_fast(s[x][r] - mu);
-            l[r] += p;
-            axpy16B<false>(o[r], p, R.vv[b * SB + x]);
-          }
+        for (int x = 0; x < SB; ++x) {
+          const float p = exp2_fast(s[x][r] - mu);
+          l[r] += p;
+          axpy16B(o[r], p, R.vv[b * SB + x]);
         }
       }
     }
-  }
-}
-
-// Query rows of the prefix work item of prompt p, KV head g (rows
-// slot_in_prompt * hpk + j; rows of idle slots and padding rows are zero).
-template <class SH, int PR>
-__device__ __forceinline__ void load_prefix_q(const StepArgs& a, const LayerView& V, int p, int g, u32x4 (&q)[PR]) {
-  constexpr int HPK = SH::HPK;
-  const int ch = (threadIdx.x & 63) % SH::LPT;
-#pragma unroll
-  for (int r = 0; r < PR; ++r) {
-    const int si = r / HPK, j = r - si * HPK, s = p * a.m + min(si, a.m - 1);
-    if (r < a.prefix_rows && a.slot[s].len > 0)
-      q[r] = *((const u32x4*)(V.q + ((int64_t)s * a.Hq + g * HPK + j) * SH::ROWB) + ch);
-    else
-      q[r] = u32x4{0, 0, 0, 0};
   }
 }
 
@@ -279,41 +246,38 @@ __device__ __forceinline__ PrefixItem prefix_item(const StepArgs& a, int k) {
   return it;
 }
 
-// ---- Prefix chunk on the wavefront path (see prefix_wave) -------------------
+// ---- Prefix chunk on row tiles (see prefix_rows) ----------------------------
 template <class SH, bool L2>
-struct PrefixWave {
-  using Regs = WaveRegs<SH, SH::PR>;
-  static constexpr int kLoads = 2 * Regs::U;  // load instructions of issue()
+struct PrefixTile {
+  using T = RowTile<SH, SH::PR>;
+  using Regs = typename T::Regs;
   __device__ __forceinline__ static void range(const StepArgs& a, const PrefixItem& it, int& wt0, int& wt1) {
-    const int w = threadIdx.x >> 6, sub = a.prefix_split / 4;
+    const int w = threadIdx.x >> 6, sub = a.prefix_split / kWaves;
     wt0 = min(it.t0 + w * sub, it.t1);
     wt1 = min(wt0 + sub, it.t1);
-  }
-  __device__ __forceinline__ static PrefixAddr<SH> addr(const StepArgs& a, const LayerView& V, int p, int g) {
-    const int64_t head = ((int64_t)p * a.Hkv + g) * 2;
-    return PrefixAddr<SH>{{V.prefix + head * a.max_prompt_len * SH::KROWB,
-                           V.prefix + (head + 1) * a.max_prompt_len * SH::KROWB}};
   }
   // Loads of the first round (also for an empty range: in bounds, masked).
   __device__ __forceinline__ static void issue(const StepArgs& a, const LayerView& V, const PrefixItem& it, int g, Regs& R) {
     int wt0, wt1;
     range(a, it, wt0, wt1);
-    wave_load_round<SH, SH::PR>(addr(a, V, it.p, g), wt0, wt1, wt0, R);
+    T::load_round(PrefixRows<SH>(a, V.prefix, it.p, g, wt1), wt0, R);
   }
   template <class Before, class After>
   __device__ __forceinline__ static void finish(const StepArgs& a, const LayerView& V, const PrefixItem& it, int g, float* smem,
                                 Regs& R, Before&& before, After&& after_stores) {
-    constexpr int PR = SH::PR;
     int wt0, wt1;
     range(a, it, wt0, wt1);
     before();
-    u32x4 q[PR];
-    load_prefix_q<SH, PR>(a, V, it.p, g, q);
-    float m[PR], l[PR], o[PR][SH::EPL];
-    wave_compute<SH, PR>(addr(a, V, it.p, g), wt0, wt1, q, a.scale_log2, R, m, l, o);
-    wave_combine_groups<SH, PR>(m, l, o);
-    const int64_t rec0 = (((int64_t)it.p * a.Hkv + g) * a.prefix_chunks_max + it.c) * PR;
-    block_store_partial<SH, PR, L2>(smem, m, l, o, Exchange<L2>(a), rec0);
+    u32x4 q[T::KB];
+    T::load_q(prefix_query<SH>(a, V.q, it.p, g), q);
+    const PrefixRows<SH> ad(a, V.prefix, it.p, g, wt1);
+    typename T::Acc A;
+    T::init(A);
+    for (int base = wt0; base < wt1; base += T::TOK) {
+      if (base != wt0) T::load_round(ad, base, R);
+      T::round(R, q, base, wt1, a.scale_log2, A);
+    }
+    T::template store<L2>(smem, A, Exchange<L2>(a), (((int64_t)it.p * a.Hkv + g) * a.prefix_chunks_max + it.c) * SH::PR);
     after_stores();
   }
 };
@@ -585,10 +549,6 @@ struct Resp {
     if (r.has_new) {
       knew = *((const u32x4*)(V.knew + newrow) + ch);
       vnew = *((const u32x4*)(V.vnew + newrow) + ch);
-      if constexpr (SH::KV8) {
-        knew = widen_e4m3(narrow_e4m3(knew));
-        vnew = widen_e4m3(narrow_e4m3(vnew));
-      }
     }
     SuffixAddr<SH> ad{(const char*)V.pool, pages, a.Hkv, g};
     float m[HPK], l[HPK], o[HPK][SH::EPL];
@@ -660,6 +620,48 @@ struct RespTiles {
     RM::publish(smem, A);
     const int64_t rec0 = prefix_records(a, SH::PR) + (((int64_t)r.s * a.Hkv + g) * a.suffix_chunks_max + r.c) * HPK;
     combine_store_partial<SH, HPK, L2>(smem, Exchange<L2>(a), rec0);
+    after_stores();
+  }
+};
+
+// The same response item on a row tile (fp32 pages; see suffix_chunk_rows).
+template <class SH, bool L2>
+struct RespRows {
+  static constexpr int HPK = SH::HPK;
+  using T = RowTile<SH, HPK>;
+  using Regs = typename T::Regs;
+  __device__ __forceinline__ static void issue(const StepArgs& a, const LayerView& V, const RespItem& r, int pages, int g, Regs& R) {
+    T::load_round(PageRows<SH>{V.pool, pages, a.Hkv, g, r.wt0}, r.wt0, R);
+  }
+  template <class Before, class After>
+  __device__ __forceinline__ static void finish(const StepArgs& a, const LayerView& V, const RespItem& r, int pages, int g,
+                                float* smem, Regs& R, Before&& before, After&& after_stores) {
+    const SlotPlan& sp = a.slot[r.s];
+    const int te = r.has_new ? r.last : r.wt1, row = threadIdx.x & 15;
+    before();
+    u32x4 q[T::KB];
+    T::load_q(row < HPK ? V.q + ((int64_t)r.s * a.Hq + g * HPK + row) * SH::ROWB : nullptr, q);
+    typename T::Acc A;
+    if (r.has_new) {
+      const int64_t newrow = ((int64_t)r.s * a.Hkv + g) * SH::ROWB;
+      T::start_row(V.knew + newrow, V.vnew + newrow, q, a.scale_log2, A);
+      store_row<SH>(V.pool + (int64_t)(sp.cur_page * a.Hkv + g) * 2 * SH::PAGEB + (r.last & 15) * SH::KROWB, V.knew + newrow,
+                    V.vnew + newrow);
+    } else {
+      T::init(A);
+    }
+    const PageRows<SH> ad{V.pool, pages, a.Hkv, g, r.wt0};
+    for (int base = r.wt0; base < te; base += T::TOK) {
+      if (base != r.wt0) T::load_round(ad, base, R);
+      T::round(R, q, base, te, a.scale_log2, A);
+    }
+    if (V.layer == 0 && r.tail && g == 0 && threadIdx.x == 0) {
+      // bookkeeping of this step's token, once per step (its K/V are stored above)
+      a.page_table[(int64_t)sp.seq * a.pages_per_slot + (r.last >> 4)] = sp.cur_page;
+      __hip_atomic_fetch_add(&a.tokens[(r.s / a.m) * a.G + sp.sample], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    T::template store<L2>(smem, A, Exchange<L2>(a),
+                          prefix_records(a, SH::PR) + (((int64_t)r.s * a.Hkv + g) * a.suffix_chunks_max + r.c) * HPK);
     after_stores();
   }
 };
@@ -821,7 +823,7 @@ template <class SH, bool L2>
 __device__ __forceinline__ void prefix_loop(const StepArgs& a, int g, int jp, float* smem) {
   if (jp >= a.n_prefix_items) return;
   const int nk = (a.n_prefix_items - jp + a.n_pre_wg - 1) / a.n_pre_wg;
-  using P = std::conditional_t<SH::MFMA, PrefixMfma<SH, L2>, PrefixWave<SH, L2>>;
+  using P = std::conditional_t<SH::MFMA, PrefixMfma<SH, L2>, PrefixTile<SH, L2>>;
   typename P::Regs R;
   for (int l = 0; l < a.num_layers; ++l) {
     const LayerView V = layer_view(a, l);
@@ -852,7 +854,8 @@ template <class SH, bool L2>
 __device__ __forceinline__ void suffix_loop(const StepArgs& a, int g, int jr, float* smem) {
   if (jr >= a.n_suffix_items) return;
   const int nk = (a.n_suffix_items - jr + a.n_suf_wg - 1) / a.n_suf_wg;
-  using P = std::conditional_t<SH::BF, RespTiles<SH, L2>, Resp<SH, L2>>;
+  using P = std::conditional_t<SH::BF, RespTiles<SH, L2>,
+                             std::conditional_t<SH::RESP_ROWS, RespRows<SH, L2>, Resp<SH, L2>>>;
   typename P::Regs R;
   RespItem it = resp_item(a, jr);
   int pages = resp_pages(a, it);
