@@ -482,10 +482,10 @@ struct RespItem {
   bool has_new;  // this wavefront's range holds the newest token
   bool tail;     // the item is the slot's last piece
 };
-__device__ __forceinline__ RespItem resp_item(const StepArgs& a, int it) {
-  // The slot of response item `it`: slots' first items never decrease and an
-  // idle slot adds none, so it is the last slot whose first item is <= it.  A
-  // binary search with uniform indices reads the plan with scalar loads only.
+// The slot of response item `it`: slots' first items never decrease and an
+// idle slot adds none, so it is the last slot whose first item is <= it.  A
+// binary search with uniform indices reads the plan with scalar loads only.
+__device__ __forceinline__ int response_slot(const StepArgs& a, int it) {
   int lo = 0, hi = a.S - 1;
   while (lo < hi) {
     const int mid = __builtin_amdgcn_readfirstlane((lo + hi + 1) >> 1);
@@ -494,7 +494,10 @@ __device__ __forceinline__ RespItem resp_item(const StepArgs& a, int it) {
     else
       hi = mid - 1;
   }
-  const int s = __builtin_amdgcn_readfirstlane(lo);
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+__device__ __forceinline__ RespItem resp_item(const StepArgs& a, int it) {
+  const int s = response_slot(a, it);
   RespItem r;
   r.s = s;
   r.c = it - a.slot[s].item_begin;
@@ -785,26 +788,32 @@ __device__ __forceinline__ void peer_mark(const StepArgs& a, int l, int w) {
 // any gets a second, so work-group b shares its CU with b +- gridDim.x / 2,
 // which for KV head g is index j +- nj / 2; the pair waits only when the CU
 // ids they recorded at their start agree.
-__device__ void mate_gate(const StepArgs& a, int l) {
+// One wavefront's part: w indexes the mate's progress words.
+__device__ __forceinline__ void mate_wait(const StepArgs& a, int l, int w) {
   const int nj = gridDim.x / a.Hkv;
-  if (threadIdx.x < kWaves && (nj & 1) == 0 && a.merge_polls >= 0) {
+  if ((threadIdx.x & 63) == 0 && (nj & 1) == 0 && a.merge_polls >= 0) {
     const int g = blockIdx.x % a.Hkv, j = blockIdx.x / a.Hkv;
     const int jm = j < nj / 2 ? j + nj / 2 : j - nj / 2;
-    const int w = threadIdx.x;
     // a merge mate is not waited for: its part of the layer comes last (the host places merges
-    // opposite prefix work-groups, which load their next layer only when it may start)
+    // opposite prefix work-groups)
     int im;
     const int rm = wg_role(a, jm, im);
-    const bool need = w == 0 && (rm == 0 ? im < a.n_prefix_items : rm == 1 ? im < a.n_suffix_items : false);
+    const bool one = a.resp_cut == 2;  // each wavefront of a response work-group has a word of its own
+    const bool need = rm == 0 ? im < a.n_prefix_items : rm == 1 ? (one ? im * kWaves + w : im) < a.n_suffix_items : false;
+    const int word = rm == 1 && one ? w : 0;
     const int32_t* line = peer_line(a, jm * a.Hkv + g);
     if (need && __hip_atomic_load(line + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == cu_id() + 1) {
       const int32_t target = (int32_t)((uint32_t)a.peer_base + (uint32_t)l + 1u);
       const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-      while (__hip_atomic_load(line + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target < 0 &&
+      while (__hip_atomic_load(line + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target < 0 &&
              __builtin_amdgcn_s_memrealtime() - t0 < (uint64_t)kMateWaitTicks)
         __builtin_amdgcn_s_sleep(2);
     }
   }
+  asm volatile("" ::: "memory");
+}
+__device__ void mate_gate(const StepArgs& a, int l) {
+  if (threadIdx.x < 64) mate_wait(a, l, 0);
   __syncthreads();
 }
 
@@ -890,6 +899,76 @@ __device__ __forceinline__ void suffix_loop(const StepArgs& a, int g, int jr, fl
   }
 }
 
+// One wavefront of a response work-group with a piece of its own
+// (StepArgs::resp_cut == 2): item `it` of every layer, from loads to arrival,
+// apart from the other wavefronts.
+template <class SH, bool L2>
+__device__ __forceinline__ void suffix_wave_loop(const StepArgs& a, int g, int it) {
+  using RM = RespMfma<SH>;
+  constexpr int D = SH::D, HPK = SH::HPK;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, h = lane >> 4;
+  const int s = response_slot(a, it), p = s / a.m;
+  const SlotPlan& sp = a.slot[s];
+  const int c = it - sp.item_begin, len = sp.len, last = len - 1;
+  const int npages = (len + kPageTokens - 1) / kPageTokens;
+  const int pg0 = piece_first_page(c, npages, sp.pieces), pg1 = piece_first_page(c + 1, npages, sp.pieces);
+  const bool tail = pg1 == npages;  // holds the newest token
+  const int t0 = pg0 * kPageTokens, te = tail ? last : pg1 * kPageTokens;  // stored tokens of the piece
+  const int pages = lane < pg1 - pg0 ? a.page_table[(int64_t)sp.seq * a.pages_per_slot + pg0 + lane] : 0;
+  const int64_t rec0 = prefix_records(a, SH::PR) + (((int64_t)s * a.Hkv + g) * a.suffix_chunks_max + c) * HPK;
+  const Exchange<L2> ex(a);
+  typename RM::Regs R;
+  RM::load_round(layer_view(a, 0).pool, pages, a.Hkv, g, 0, R);
+  for (int l = 0; l < a.num_layers; ++l) {
+    const LayerView V = layer_view(a, l);
+    if (l > 0 && lane == 0) {
+      const int32_t target = (int32_t)((uint32_t)a.merged_base[p] + (uint32_t)l * (uint32_t)a.merged_per_layer[p]);
+      if (!bounded_wait(a, layer_flag(a, p, g), target))
+        __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("" ::: "memory");  // what follows is read after the wait
+    bf16x8 bq[SH::KB];
+    RM::load_q(V.q, (int64_t)s * a.Hq + g * HPK, bq);
+    typename RM::Acc A;
+    if (tail) {
+      typename RM::NewRows N;
+      const int64_t newrow = ((int64_t)s * a.Hkv + g) * SH::ROWB;
+      RM::load_new(V.knew + newrow, V.vnew + newrow, N);
+      RM::round_new(N);
+      RM::start_new(N, bq, a.scale_log2, A);
+      RM::store_new((char*)RM::page(V.pool, sp.cur_page, a.Hkv, g), last & 15, N);
+    } else {
+      RM::init(A);
+    }
+    for (int base = t0; base < te; base += RM::TOK) {
+      if (base != t0) RM::load_round(V.pool, pages, a.Hkv, g, (base - t0) >> 4, R);
+      RM::round(R, bq, base, te, a.scale_log2, A);
+    }
+    if (l == 0 && tail && g == 0 && lane == 0) {
+      // bookkeeping of this step's token, once per step (its K/V are stored above)
+      a.page_table[(int64_t)sp.seq * a.pages_per_slot + (last >> 4)] = sp.cur_page;
+      __hip_atomic_fetch_add(&a.tokens[p * a.G + sp.sample], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (col < HPK) {
+#pragma unroll
+      for (int db = 0; db < SH::DB; ++db) ex.store4((uint32_t)(((rec0 + col) * D + db * 16 + h * 4) * 4), A.o[db]);
+      if (h == 0) ex.store_ml(rec0 + col, A.m, A.lt[0]);
+    }
+    // counted once this wavefront's stores have completed
+    asm volatile("" ::: "memory");
+    wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    if (lane == 0) {
+      __hip_atomic_fetch_add(slot_counter(a, s, g), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      peer_mark(a, l, w);
+    }
+    if (l + 1 < a.num_layers) {
+      mate_wait(a, l, w);
+      RM::load_round(layer_view(a, l + 1).pool, pages, a.Hkv, g, 0, R);
+    }
+  }
+}
+
 template <class SH, bool L2>
 __device__ void merge_loop(const StepArgs& a, int g, int mj) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -945,8 +1024,15 @@ __global__ __launch_bounds__(kBlockThreads, SH::MIN_WAVES) void layers_kernel(co
   const int role = wg_role(a, j, idx);
   if (role == 0)
     prefix_loop<SH, L2>(a, g, idx, smem);
-  else if (role == 1)
-    suffix_loop<SH, L2>(a, g, idx, smem);
+  else if (role == 1) {
+    bool waves = false;
+    if constexpr (SH::BF) {
+      waves = a.resp_cut == 2;
+      const int it = __builtin_amdgcn_readfirstlane(idx * kWaves + (int)(threadIdx.x >> 6));
+      if (waves && it < a.n_suffix_items) suffix_wave_loop<SH, L2>(a, g, it);
+    }
+    if (!waves) suffix_loop<SH, L2>(a, g, idx, smem);
+  }
   else
     merge_loop<SH, L2>(a, g, idx);
   if (a.clock_start) {

@@ -841,10 +841,14 @@ infs_status launch_step_layers(infs_ctx* c, const KernelKey& key, StepArgs& a, i
   // and response pieces so that no producer reads many more tokens than the others.
   int32_t lens[infs::kMaxSlots], pieces[infs::kMaxSlots];
   for (int s = 0; s < a.S; ++s) lens[s] = a.slot[s].len;
-  const infs::StepRoles roles =
-      c->step_split ? infs::plan_step_roles(nj, a.S, a.n_prefix_items, a.prefix_split, lens, c->split, c->scmax,
-                                            pieces)
-                    : infs::plan_step_roles_chunks(nj, a.S, a.n_prefix_items, lens, c->split, pieces);
+  infs::StepRoles roles;
+  const bool waves = c->step_split && key.bf16 &&
+                     infs::plan_step_waves(nj, a.S, a.num_prompts, a.n_prefix_items, a.prefix_split, lens, c->split,
+                                           c->scmax, pieces, &roles);
+  if (!waves)
+    roles = c->step_split ? infs::plan_step_roles(nj, a.S, a.n_prefix_items, a.prefix_split, lens, c->split, c->scmax,
+                                                  pieces)
+                          : infs::plan_step_roles_chunks(nj, a.S, a.n_prefix_items, lens, c->split, pieces);
   if ((a.n_prefix_items > 0 && roles.n_pre < 1) || (roles.n_suffix_items > 0 && roles.n_suf < 1))
     return fail(c, INFS_E_STATE, "no step launch on this device: %d work-groups per KV head cannot take prefix "
                 "chunks, response chunks and merges", nj);
@@ -857,7 +861,7 @@ infs_status launch_step_layers(infs_ctx* c, const KernelKey& key, StepArgs& a, i
     items += pieces[s];
   }
   a.n_suffix_items = roles.n_suffix_items;
-  a.resp_cut = roles.cut ? 1 : 0;
+  a.resp_cut = waves ? 2 : roles.cut ? 1 : 0;
   // Merges go opposite the prefix work-groups (index j shares its CU with j + nj/2, see
   // mate_gate), else after the response work-groups.
   a.merge_j0 = (nj % 2 == 0 && a.n_pre_wg <= nj / 2 && a.n_merge_wg <= nj / 2) ? nj / 2 : a.n_pre_wg + a.n_suf_wg;

@@ -45,8 +45,8 @@ struct StepRoles {
 
 namespace step_plan_detail {
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-inline int pieces_at(int pages, int scmax, int t) {
-  const int lo = cdiv(pages, kPiecePagesMax), hi = pages < scmax ? pages : scmax;
+inline int pieces_at(int pages, int scmax, int t, int page_max) {
+  const int lo = cdiv(pages, page_max), hi = pages < scmax ? pages : scmax;
   int n = cdiv(pages, t);
   if (n < lo) n = lo;
   if (n > hi) n = hi;
@@ -55,21 +55,21 @@ inline int pieces_at(int pages, int scmax, int t) {
 }  // namespace step_plan_detail
 
 // Cut the live responses (len[s] > 0 tokens, s < S) into at most w pieces in
-// total, each slot into at most scmax and at least ceil(pages / kPiecePagesMax),
+// total, each slot into at most scmax and at least ceil(pages / page_max),
 // with the largest piece as small as it can be (pieces of at least
 // kPiecePagesMin pages where a response has them).  Writes pieces[s] (0 for an
 // idle slot) and returns the largest piece in pages, or -1 when the slots
 // cannot fit in w pieces.
-inline int cut_responses(const int32_t* len, int S, int w, int scmax, int32_t* pieces) {
+inline int cut_responses(const int32_t* len, int S, int w, int scmax, int32_t* pieces, int page_max = kPiecePagesMax) {
   using namespace step_plan_detail;
   auto total = [&](int t) {
     int n = 0;
     for (int s = 0; s < S; ++s)
-      if (len[s] > 0) n += pieces_at(cdiv(len[s], kPageTokens), scmax, t);
+      if (len[s] > 0) n += pieces_at(cdiv(len[s], kPageTokens), scmax, t, page_max);
     return n;
   };
-  if (total(kPiecePagesMax) > w) return -1;
-  int lo = kPiecePagesMin, hi = kPiecePagesMax;  // smallest t with total(t) <= w
+  if (total(page_max) > w) return -1;
+  int lo = kPiecePagesMin, hi = page_max;  // smallest t with total(t) <= w
   while (lo < hi) {
     const int mid = (lo + hi) / 2;
     if (total(mid) <= w)
@@ -82,7 +82,7 @@ inline int cut_responses(const int32_t* len, int S, int w, int scmax, int32_t* p
     pieces[s] = 0;
     if (len[s] <= 0) continue;
     const int pages = cdiv(len[s], kPageTokens);
-    pieces[s] = pieces_at(pages, scmax, lo);
+    pieces[s] = pieces_at(pages, scmax, lo, page_max);
     const int big = cdiv(pages, pieces[s]);
     if (big > largest) largest = big;
   }
@@ -125,6 +125,69 @@ inline bool longer_prefix_chunks(int nj, int S, int n_prefix_items, const int32_
   int32_t pieces[kMaxSlots];
   const StepRoles r = plan_step_roles_chunks(nj, S, n_prefix_items, len, split, pieces);
   return r.n_suffix_items > r.n_suf || r.n_pre < n_prefix_items;
+}
+
+// The split of a step with one response piece per wavefront (bf16 and E4M3
+// pages): the four wavefronts of a response work-group take a piece each, of
+// whichever slots, and hand in a partial each, without a barrier or a combine
+// between them.  With many slots the work-group pieces of plan_step_roles are
+// dealt several to a work-group, each loaded, combined and counted in turn;
+// here every wavefront has one.  The price is four times the partials, which
+// few slots with long responses pay in their merges.  Measured before and with
+// it, us a step; 36 layers, 4 prompts (256 to 4096 tokens), 32/8 heads: 64 slots
+// of responses up to 256 tokens 1179 and 835, up to 1024 tokens 1804 and 1353,
+// up to 2048 tokens 2749 and 2308; 48 slots up to 700 tokens 1422 and 977; 36
+// slots up to 700 tokens 985 and 844.  One prompt of 1024 tokens, 28 layers, 16/8
+// heads: 64 slots up to 1000 tokens 1011 and 837, 40 slots up to 1500 tokens 1049
+// and 778; but 32 slots up to 2048 tokens 860 and 923, 16 slots up to 2048 tokens
+// 472 and 621, and with few per-layer chunks to a response work-group 64 slots
+// up to 300 tokens (1.6 chunks) 697 and 716, 40 slots up to 600 tokens (1.3) 611
+// and 678.  Hence more than kWaveMinSlots slots and kWaveMinItems4 / 4 chunks.
+//
+// A merge work-group only waits while the others load, so the merges run on
+// fewer than one wavefront each: two to a wavefront, and four where several
+// prompts walk the layers on their own, unless the responses are deep
+// (kWaveDeepItems chunks and more).  One, two, four merges to a wavefront: one
+// prompt, 64 slots up to 1000 tokens 1114, 837, 913; 4 prompts, 64 slots up to
+// 512 tokens 1142, 1203, 961, up to 2048 tokens 2534, 2243, 2450.
+// The prefix is weighed kWavePrefixCost halves, as its chunks are walked after
+// the layer's queries arrive.
+// False where it does not apply: few slots or chunks, or pieces that would not
+// fit a wavefront.
+constexpr int kWaveMinSlots = 32, kWaveMinItems4 = 7, kWaveDeepItems = 5, kWavePrefixCost = 3;
+constexpr int kWavePagesMax = 64;  // a wavefront holds the page numbers of its piece one per lane
+inline bool plan_step_waves(int nj, int S, int prompts, int n_prefix_items, int prefix_split, const int32_t* len, int split, int scmax,
+                            int32_t* pieces, StepRoles* out) {
+  using namespace step_plan_detail;
+  StepRoles r = plan_step_roles_chunks(nj, S, n_prefix_items, len, split, pieces);
+  if (S <= kWaveMinSlots || 4 * r.n_suffix_items < kWaveMinItems4 * r.n_suf) return false;
+  const int merges = prompts > 1 && r.n_suffix_items < kWaveDeepItems * r.n_suf ? 4 : 2;  // to a wavefront
+  r.n_merge = cdiv(S, merges * kWaves) < nj - 1 ? cdiv(S, merges * kWaves) : nj - 1;
+  const int prod = nj - r.n_merge;
+  int best = -1, best_pre = 0;
+  const int kmax = n_prefix_items > 0 ? n_prefix_items : 1;
+  for (int k = 1; k <= kmax; ++k) {
+    const int n_pre = n_prefix_items > 0 ? cdiv(n_prefix_items, k) : 0;
+    const int w = prod - n_pre;
+    if (w < 1) continue;
+    const int big = cut_responses(len, S, w * kWaves, scmax, pieces, kWavePagesMax);
+    if (big <= 0) continue;
+    const int pre_tokens = kWavePrefixCost * k * prefix_split / 2, resp_tokens = big * kPageTokens * kWaves;
+    const int cost = pre_tokens > resp_tokens ? pre_tokens : resp_tokens;
+    if (best < 0 || cost < best) {
+      best = cost;
+      best_pre = n_pre;
+    }
+  }
+  if (best < 0) return false;
+  r.n_pre = best_pre;
+  r.n_suf = prod - best_pre;
+  cut_responses(len, S, r.n_suf * kWaves, scmax, pieces, kWavePagesMax);
+  r.cut = true;
+  r.n_suffix_items = 0;
+  for (int s = 0; s < S; ++s) r.n_suffix_items += pieces[s];
+  *out = r;
+  return true;
 }
 
 // Roles of the nj work-groups per KV head and the response pieces of a step.

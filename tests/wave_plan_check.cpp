@@ -1,0 +1,58 @@
+// Host check of the wavefront split of a step launch (plan_step_waves in
+// csrc/step_plan.h), built with g++ by tests/test_wave_plan.py: over random slot
+// lengths and launch shapes, the roles add up, there is a wavefront for every
+// item, every live response's pieces are whole page ranges that tile it, and
+// pieces stay within the limits per slot and per wavefront.
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <vector>
+
+#include "step_plan.h"
+
+using namespace infs;
+
+static int fails = 0;
+#define CHECK(cond)                                                             \
+  do {                                                                          \
+    if (!(cond) && ++fails < 20) std::printf("case %d FAIL %s\n", cs, #cond);   \
+  } while (0)
+
+int main() {
+  std::mt19937 rng(7);
+  auto uni = [&](int a, int b) { return std::uniform_int_distribution<int>(a, b)(rng); };
+  int applied = 0;
+  for (int cs = 0; cs < 20000; ++cs) {
+    const int nj = (int[]){2, 3, 8, 32, 63, 64, 128}[uni(0, 6)], S = uni(1, kMaxSlots), split = (int[]){128, 256, 512}[uni(0, 2)];
+    const int cap = uni(0, 2) ? uni(1, 4096) : uni(1, 20000), idle = uni(0, 3) ? 0 : uni(0, 90);
+    const int scmax = (cap + split - 1) / split, npi = uni(0, 64);
+    std::vector<int32_t> len(S, 0), pieces(S, -1);
+    for (int s = 0; s < S; ++s)
+      if (uni(0, 99) >= idle) len[s] = uni(1, cap);
+    StepRoles r{};
+    if (!plan_step_waves(nj, S, uni(1, 4), npi, 256, len.data(), split, scmax, pieces.data(), &r)) continue;
+    ++applied;
+    CHECK(S > kWaveMinSlots && r.cut);
+    CHECK(r.n_merge >= 1 && r.n_suf >= 1 && r.n_pre >= (npi > 0) && r.n_pre <= npi);
+    CHECK(r.n_pre + r.n_suf + r.n_merge == nj);
+    int items = 0;
+    for (int s = 0; s < S; ++s) {
+      if (len[s] == 0) {
+        CHECK(pieces[s] == 0);
+        continue;
+      }
+      const int pages = (len[s] + kPageTokens - 1) / kPageTokens, n = pieces[s];
+      CHECK(n >= 1 && n <= pages && n <= scmax);
+      if (n < 1) continue;
+      items += n;
+      CHECK(piece_first_page(0, pages, n) == 0 && piece_first_page(n, pages, n) == pages);
+      for (int c = 0; c < n; ++c) {
+        const int p = piece_first_page(c + 1, pages, n) - piece_first_page(c, pages, n);
+        CHECK(p >= 1 && p <= kWavePagesMax);
+      }
+    }
+    CHECK(items == r.n_suffix_items && items <= r.n_suf * kWaves);
+  }
+  std::printf("applied %d failures %d\n", applied, fails);
+  return fails || applied < 1000;
+}
