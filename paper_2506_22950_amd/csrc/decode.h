@@ -1600,7 +1600,153 @@ __device__ void merge_block(const StepArgs& a, int s, int g, unsigned long long*
   merge_outputs<SH, L2>(a, s, g, smem);
 }
 
+// One lane: wait until *ctr has reached target, polling at most merge_polls
+// times.  Gives up at once when merge_polls < 0 or, in a step launch,
+// when the status word shows that another wait has given up.
+__device__ bool bounded_wait(const StepArgs& a, const int32_t* ctr, int32_t target, bool step) {
+  if (a.merge_polls < 0) return false;
+  if (reached(ctr, target)) return true;
+  if (step && __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
+  for (int spins = 0; spins < a.merge_polls; ++spins) {
+    __builtin_amdgcn_s_sleep(2);
+    if (reached(ctr, target)) return true;
+  }
+  return false;
+}
+
+
+// One wavefront merges every partial of (slot s, KV head g) of a layer and
+// writes O rows g*hpk .. +hpk-1 (the log-sum-exp combination of the split-K
+// partial softmaxes, in partial order).  Lane x of vector v holds outputs
+// 4 * (v * 64 + x) .. +3; partials are loaded MCW at a time.
+// STEP: one of many layers, so partials are read past the CU's L1 (records of the
+// layer before may be there).
+template <class SH>
+struct MergeWaveShape {
+  static constexpr int OPP = SH::HPK * SH::D;
+  static constexpr int MV = (OPP / 4 + 63) / 64;
+  static constexpr int MCW = MV == 1 ? 24 : MV == 2 ? 8 : 4;
+};
+
+template <class SH, bool L2, bool STEP>
+__device__ void merge_wave(const StepArgs& a, float* out, int s, int g, int32_t target) {
+  using MW = MergeWaveShape<SH>;
+  constexpr int D = SH::D, HPK = SH::HPK, MV = MW::MV, MCW = MW::MCW;
+  const int lane = threadIdx.x & 63;
+  const int p = s / a.m, si = s - p * a.m;
+  float* orow = out + ((int64_t)s * a.Hq + g * HPK) * D;
+  int ok = 0;
+  if (lane == 0) {
+    ok = bounded_wait(a, slot_counter(a, s, g), target, STEP);
+    if (!ok) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  ok = __builtin_amdgcn_readfirstlane(ok);
+  if (!ok) {
+#pragma unroll
+    for (int v = 0; v < MV; ++v) {
+      const int x = (v * 64 + lane) * 4;
+      if (x < MW::OPP) *(f32x4*)(orow + x) = f32x4{1.f, 1.f, 1.f, 1.f} * __builtin_nanf("");
+    }
+    return;
+  }
+  const int nP = a.prompt[p].nchunks;
+  const int n = nP + a.slot[s].pieces;
+  const int64_t pbase = ((int64_t)p * a.Hkv + g) * a.prefix_chunks_max * SH::PR + si * HPK;
+  const int64_t sbase = prefix_records(a, SH::PR) + ((int64_t)s * a.Hkv + g) * a.suffix_chunks_max * HPK;
+  auto rec = [&](int c, int j) -> int64_t { return (c < nP ? pbase + (int64_t)c * SH::PR : sbase + (int64_t)(c - nP) * HPK) + j; };
+  const Exchange<L2, STEP> ex(a);
+  float M[MV], L[MV];
+  f32x4 O[MV];
+#pragma unroll
+  for (int v = 0; v < MV; ++v) {
+    M[v] = NEG_INF;
+    L[v] = 0.f;
+    O[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int c0 = 0; c0 < n; c0 += MCW) {
+    u32x2 ml[MCW][MV];
+    f32x4 ov[MCW][MV];
+#pragma unroll
+    for (int u = 0; u < MCW; ++u) {
+      const int c = c0 + u;
+#pragma unroll
+      for (int v = 0; v < MV; ++v) {
+        const int x = (v * 64 + lane) * 4, j = x / D, d = x - j * D;
+        if (c < n && x < MW::OPP) {
+          const int64_t r = rec(c, j);
+          ml[u][v] = ex.load_ml(r);
+          ov[u][v] = ex.load4((uint32_t)((r * D + d) * 4));
+        } else {
+          ml[u][v] = u32x2{__float_as_uint(NEG_INF), 0u};
+          ov[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < MCW; ++u)
+#pragma unroll
+      for (int v = 0; v < MV; ++v) {
+        const float mc = __uint_as_float(ml[u][v].x), lc = __uint_as_float(ml[u][v].y);
+        const float nm = fmaxf(M[v], mc);
+        const float base = nm == NEG_INF ? 0.f : nm;
+        const float al = exp2_fast(M[v] - base), be = mc == NEG_INF ? 0.f : exp2_fast(mc - base);
+        L[v] = L[v] * al + lc * be;
+        O[v] = O[v] * al + ov[u][v] * be;
+        M[v] = nm;
+      }
+  }
+#pragma unroll
+  for (int v = 0; v < MV; ++v) {
+    const int x = (v * 64 + lane) * 4;
+    if (x < MW::OPP) *(f32x4*)(orow + x) = O[v] * (1.f / L[v]);
+  }
+}
+
+// One wavefront takes the whole response of slot s (bf16 and E4M3 pages; see
+// StepArgs::resp_cut), from loads to arrival, apart from the other wavefronts.
 template <class SH, bool L2>
+__device__ void suffix_slot_wave(const StepArgs& a, int s, int g) {
+  using RM = RespMfma<SH>;
+  constexpr int D = SH::D, HPK = SH::HPK;
+  const int lane = threadIdx.x & 63, col = lane & 15, h = lane >> 4;
+  const SlotPlan& sp = a.slot[s];
+  const int last = sp.len - 1, npages = (sp.len + kPageTokens - 1) / kPageTokens;
+  int32_t* ptab = a.page_table + (int64_t)sp.seq * a.pages_per_slot;
+  const int pages = lane < npages ? ptab[lane] : 0;
+  typename RM::Regs R;
+  RM::load_round((const char*)a.pool, pages, a.Hkv, g, 0, R);
+  bf16x8 bq[SH::KB];
+  RM::load_q(a.q, (int64_t)s * a.Hq + g * HPK, bq);
+  typename RM::NewRows N;
+  const int64_t newrow = ((int64_t)s * a.Hkv + g) * SH::ROWB;
+  RM::load_new((const char*)a.knew + newrow, (const char*)a.vnew + newrow, N);
+  typename RM::Acc A;
+  RM::round_new(N);
+  RM::start_new(N, bq, a.scale_log2, A);
+  RM::store_new((char*)RM::page((const char*)a.pool, sp.cur_page, a.Hkv, g), last & 15, N);
+  for (int base = 0; base < last; base += RM::TOK) {
+    if (base != 0) RM::load_round((const char*)a.pool, pages, a.Hkv, g, base >> 4, R);
+    RM::round(R, bq, base, last, a.scale_log2, A);
+  }
+  if (g == 0 && lane == 0) {  // bookkeeping of this step's token (K/V stored above)
+    ptab[last >> 4] = sp.cur_page;
+    if (a.count_tokens)
+      __hip_atomic_fetch_add(&a.tokens[(s / a.m) * a.G + sp.sample], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const Exchange<L2> ex(a);
+  const int64_t rec0 = prefix_records(a, SH::PR) + ((int64_t)s * a.Hkv + g) * a.suffix_chunks_max * HPK;
+  if (col < HPK) {
+#pragma unroll
+    for (int db = 0; db < SH::DB; ++db) ex.store4((uint32_t)(((rec0 + col) * D + db * 16 + h * 4) * 4), A.o[db]);
+    if (h == 0) ex.store_ml(rec0 + col, A.m, A.lt[0]);
+  }
+  // counted once this wavefront's stores have completed
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_s_waitcnt(0);
+  if (lane == 0) __hip_atomic_fetch_add(slot_counter(a, s, g), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <class SH, bool L2, bool WAVES>
 __device__ __forceinline__ void decode_block(const StepArgs& a, float* smem, unsigned long long* flagp) {
   const int item = blockIdx.x / a.Hkv;
   const int g = blockIdx.x - item * a.Hkv;
@@ -1620,6 +1766,23 @@ __device__ __forceinline__ void decode_block(const StepArgs& a, float* smem, uns
     return;
   }
   int it = item - a.n_prefix_items;
+  if constexpr (WAVES) {  // live slot i's response and merge: wavefront i % 4 of work-group i / 4 of either kind
+    const int nw = (a.n_merge_items + kWaves - 1) / kWaves;
+    const int i = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (it < nw) {
+      if (it * kWaves + i < a.n_merge_items) suffix_slot_wave<SH, L2>(a, a.live_slot[it * kWaves + i], g);
+      return;
+    }
+    const int e = (it - nw - a.n_zero_items) * kWaves + i;
+    if (it >= nw + a.n_zero_items) {
+      if (e < a.n_merge_items) merge_wave<SH, L2, false>(a, a.o, a.live_slot[e], g, a.slot[a.live_slot[e]].target);
+      return;
+    }
+    const int s = a.zero_slot[it - nw];
+    float* o = a.o + ((int64_t)s * a.Hq + g * SH::HPK) * SH::D;
+    for (int idx = threadIdx.x; idx < SH::HPK * SH::D; idx += kBlockThreads) o[idx] = 0.f;
+    return;
+  }
   if (it < a.n_suffix_items) {
     const int lane = threadIdx.x & 63;
     bool hit = false;
@@ -1646,10 +1809,12 @@ __device__ __forceinline__ void decode_block(const StepArgs& a, float* smem, uns
 }
 
 // One kernel per shape and exchange policy (L2: partials through the XCD's
-// L2; the host launches the one that matches StepArgs::l2_xcds).  Timing mode
+// L2; the host launches the one that matches StepArgs::l2_xcds), and for bf16 one more
+// of each for StepArgs::resp_cut == 2 (WAVES; in one kernel it cost the other 1.5 %:
+// 28 layers, 16 slots, 439.8 against 433.3 us).  Timing mode
 // (a.clock_start != null): every block folds its start and end time (device
 // wall clock) into one of this launch's start / end slots.
-template <class SH, bool L2>
+template <class SH, bool L2, bool WAVES>
 __global__ __launch_bounds__(kBlockThreads, SH::MIN_WAVES) void decode_kernel(const StepArgs a) {
   constexpr int SMEM = SH::SMEM > MergeShape<SH>::SMEM ? SH::SMEM : MergeShape<SH>::SMEM;
   __shared__ __attribute__((aligned(16))) float smem[SMEM];
@@ -1658,7 +1823,7 @@ __global__ __launch_bounds__(kBlockThreads, SH::MIN_WAVES) void decode_kernel(co
   if (a.clock_start && threadIdx.x == 0)
     __hip_atomic_fetch_min(a.clock_start + cs, (unsigned long long)__builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-  decode_block<SH, L2>(a, smem, &flag);
+  decode_block<SH, L2, WAVES>(a, smem, &flag);
   if (a.clock_start) {
     __syncthreads();
     if (threadIdx.x == 0)

@@ -4,7 +4,7 @@
 namespace infs {
 namespace {
 
-#define INFS_ENTRY(bf, d, hpk, mf, pr) {{bf, d, hpk, mf, pr, 0}, {decode_kernel<Shape<bf, d, hpk, mf, pr>, false>, decode_kernel<Shape<bf, d, hpk, mf, pr>, true>}, {layers_kernel<Shape<bf, d, hpk, mf, pr>, false>, layers_kernel<Shape<bf, d, hpk, mf, pr>, true>}},
+#define INFS_ENTRY(bf, d, hpk, mf, pr) {{bf, d, hpk, mf, pr, 0}, INFS_KERNELS(decode_kernel, Shape<bf, d, hpk, mf, pr>), INFS_KERNELS(layers_kernel, Shape<bf, d, hpk, mf, pr>)},
 
 const KernelEntry kEntries[] = {
     INFS_ENTRY(true, 128, 1, false, 8)

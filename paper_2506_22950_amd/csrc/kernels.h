@@ -46,9 +46,11 @@ hipError_t layers_resident(const KernelKey& key, int* resident);
 // (inst_*.hip) so that they compile in parallel.
 struct KernelEntry {
   KernelKey key;
-  void (*decode[2])(const StepArgs);  // [0]: partials through the coherence point, [1]: through the XCD's L2
-  void (*layers[2])(const StepArgs);  // step launch through every layer: [0] partials through the coherence
-                                      // point, [1] through the XCD's L2
+  // [0], [2]: partials through the coherence point, [1], [3]: through the XCD's
+  // L2; [2], [3]: a wavefront takes a response piece by itself (StepArgs::resp_cut
+  // == 2; fp32: as [0], [1])
+  void (*decode[4])(const StepArgs);
+  void (*layers[4])(const StepArgs);  // step launch through every layer
 };
 struct KernelTable {
   const KernelEntry* entries;

@@ -21,6 +21,8 @@ const KernelEntry* find_entry(const KernelKey& k) {
   return nullptr;
 }
 
+int kernel_index(const StepArgs& a) { return (a.l2_xcds > 0 ? 1 : 0) + (a.resp_cut == 2 ? 2 : 0); }
+
 }  // namespace
 
 bool select_kernel(int bf16, int head_dim, int hpk, int rows, int kv8, KernelKey* key) {
@@ -52,26 +54,28 @@ int64_t prefix_elems_per_head(const KernelKey& key, int pmax_padded) {
 hipError_t launch_decode(const KernelKey& key, const StepArgs& args, int grid, hipStream_t stream) {
   const KernelEntry* e = find_entry(key);
   if (!e) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(e->decode[args.l2_xcds > 0 ? 1 : 0], dim3(grid), dim3(kBlockThreads), 0, stream, args);
+  hipLaunchKernelGGL(e->decode[kernel_index(args)], dim3(grid), dim3(kBlockThreads), 0, stream, args);
   return hipGetLastError();
 }
 
 hipError_t launch_layers(const KernelKey& key, const StepArgs& args, int grid, hipStream_t stream) {
   const KernelEntry* e = find_entry(key);
   if (!e) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(e->layers[args.l2_xcds > 0 ? 1 : 0], dim3(grid), dim3(kBlockThreads), 0, stream, args);
+  hipLaunchKernelGGL(e->layers[kernel_index(args)], dim3(grid), dim3(kBlockThreads), 0, stream, args);
   return hipGetLastError();
 }
 
 hipError_t layers_resident(const KernelKey& key, int* resident) {
   const KernelEntry* e = find_entry(key);
   if (!e) return hipErrorInvalidValue;
-  int per_cu = 0, dev = 0, cus = 0;
+  int per_cu = 0, waves_per_cu = 0, dev = 0, cus = 0;
   hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, e->layers[0], kBlockThreads, 0);
+  if (err == hipSuccess)
+    err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&waves_per_cu, e->layers[2], kBlockThreads, 0);
   if (err == hipSuccess) err = hipGetDevice(&dev);
   if (err == hipSuccess) err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (err != hipSuccess) return err;
-  *resident = per_cu * cus;
+  *resident = (per_cu < waves_per_cu ? per_cu : waves_per_cu) * cus;
   return hipSuccess;
 }
 

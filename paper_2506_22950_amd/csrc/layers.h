@@ -81,20 +81,6 @@ __device__ __forceinline__ LayerView layer_view(const StepArgs& a, int l) {
   return v;
 }
 
-// One lane: wait until *ctr has reached target, polling at most merge_polls
-// times.  Gives up at once when merge_polls < 0 or when the status word
-// shows that another wait of the launch has given up.
-__device__ bool bounded_wait(const StepArgs& a, const int32_t* ctr, int32_t target) {
-  if (a.merge_polls < 0) return false;
-  if (reached(ctr, target)) return true;
-  if (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
-  for (int spins = 0; spins < a.merge_polls; ++spins) {
-    __builtin_amdgcn_s_sleep(2);
-    if (reached(ctr, target)) return true;
-  }
-  return false;
-}
-
 // The "layer done" flag of prompt p for KV head g: the merge that completes a
 // layer of the prompt (the last one to count on its merged counter) writes the
 // counter's final value into one flag line per KV head, and producers poll the
@@ -109,7 +95,7 @@ __device__ __forceinline__ int32_t* layer_flag(const StepArgs& a, int p, int g) 
 __device__ void wait_layer(const StepArgs& a, int p, int l) {
   if (threadIdx.x == 0) {
     const int32_t target = (int32_t)((uint32_t)a.merged_base[p] + (uint32_t)l * (uint32_t)a.merged_per_layer[p]);
-    if (!bounded_wait(a, layer_flag(a, p, blockIdx.x % a.Hkv), target))
+    if (!bounded_wait(a, layer_flag(a, p, blockIdx.x % a.Hkv), target, true))
       __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
@@ -671,91 +657,6 @@ struct RespRows {
   }
 };
 
-// One wavefront merges every partial of (slot s, KV head g) of one layer and
-// writes O rows g*hpk .. +hpk-1 (the log-sum-exp combination of the split-K
-// partial softmaxes, in partial order).  Lane x of vector v holds outputs
-// 4 * (v * 64 + x) .. +3; partials are loaded MCW at a time.
-template <class SH>
-struct MergeWaveShape {
-  static constexpr int OPP = SH::HPK * SH::D;
-  static constexpr int MV = (OPP / 4 + 63) / 64;
-  static constexpr int MCW = MV == 1 ? 24 : MV == 2 ? 8 : 4;
-};
-
-template <class SH, bool L2>
-__device__ void merge_wave(const StepArgs& a, const LayerView& V, int s, int g, int32_t target) {
-  using MW = MergeWaveShape<SH>;
-  constexpr int D = SH::D, HPK = SH::HPK, MV = MW::MV, MCW = MW::MCW;
-  const int lane = threadIdx.x & 63;
-  const int p = s / a.m, si = s - p * a.m;
-  float* orow = V.o + ((int64_t)s * a.Hq + g * HPK) * D;
-  int ok = 0;
-  if (lane == 0) {
-    ok = bounded_wait(a, slot_counter(a, s, g), target);
-    if (!ok) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  ok = __builtin_amdgcn_readfirstlane(ok);
-  if (!ok) {
-#pragma unroll
-    for (int v = 0; v < MV; ++v) {
-      const int x = (v * 64 + lane) * 4;
-      if (x < MW::OPP) *(f32x4*)(orow + x) = f32x4{1.f, 1.f, 1.f, 1.f} * __builtin_nanf("");
-    }
-    return;
-  }
-  const int nP = a.prompt[p].nchunks;
-  const int n = nP + a.slot[s].pieces;
-  const int64_t pbase = ((int64_t)p * a.Hkv + g) * a.prefix_chunks_max * SH::PR + si * HPK;
-  const int64_t sbase = prefix_records(a, SH::PR) + ((int64_t)s * a.Hkv + g) * a.suffix_chunks_max * HPK;
-  auto rec = [&](int c, int j) -> int64_t { return (c < nP ? pbase + (int64_t)c * SH::PR : sbase + (int64_t)(c - nP) * HPK) + j; };
-  const Exchange<L2, true> ex(a);
-  float M[MV], L[MV];
-  f32x4 O[MV];
-#pragma unroll
-  for (int v = 0; v < MV; ++v) {
-    M[v] = NEG_INF;
-    L[v] = 0.f;
-    O[v] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  for (int c0 = 0; c0 < n; c0 += MCW) {
-    u32x2 ml[MCW][MV];
-    f32x4 ov[MCW][MV];
-#pragma unroll
-    for (int u = 0; u < MCW; ++u) {
-      const int c = c0 + u;
-#pragma unroll
-      for (int v = 0; v < MV; ++v) {
-        const int x = (v * 64 + lane) * 4, j = x / D, d = x - j * D;
-        if (c < n && x < MW::OPP) {
-          const int64_t r = rec(c, j);
-          ml[u][v] = ex.load_ml(r);
-          ov[u][v] = ex.load4((uint32_t)((r * D + d) * 4));
-        } else {
-          ml[u][v] = u32x2{__float_as_uint(NEG_INF), 0u};
-          ov[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < MCW; ++u)
-#pragma unroll
-      for (int v = 0; v < MV; ++v) {
-        const float mc = __uint_as_float(ml[u][v].x), lc = __uint_as_float(ml[u][v].y);
-        const float nm = fmaxf(M[v], mc);
-        const float base = nm == NEG_INF ? 0.f : nm;
-        const float al = exp2_fast(M[v] - base), be = mc == NEG_INF ? 0.f : exp2_fast(mc - base);
-        L[v] = L[v] * al + lc * be;
-        O[v] = O[v] * al + ov[u][v] * be;
-        M[v] = nm;
-      }
-  }
-#pragma unroll
-  for (int v = 0; v < MV; ++v) {
-    const int x = (v * 64 + lane) * 4;
-    if (x < MW::OPP) *(f32x4*)(orow + x) = O[v] * (1.f / L[v]);
-  }
-}
-
 // Role of work-group index j of a KV head (see StepArgs::merge_j0): 0 prefix,
 // 1 response, 2 merge, with its index among the work-groups of that role.
 __device__ __forceinline__ int wg_role(const StepArgs& a, int j, int& idx) {
@@ -788,7 +689,9 @@ __device__ __forceinline__ void peer_mark(const StepArgs& a, int l, int w) {
 // any gets a second, so work-group b shares its CU with b +- gridDim.x / 2,
 // which for KV head g is index j +- nj / 2; the pair waits only when the CU
 // ids they recorded at their start agree.
-// One wavefront's part: w indexes the mate's progress words.
+// One wavefront's part: w indexes the mate's progress words (WAVES:
+// each wavefront of a response work-group has one).
+template <bool WAVES>
 __device__ __forceinline__ void mate_wait(const StepArgs& a, int l, int w) {
   const int nj = gridDim.x / a.Hkv;
   if ((threadIdx.x & 63) == 0 && (nj & 1) == 0 && a.merge_polls >= 0) {
@@ -798,9 +701,8 @@ __device__ __forceinline__ void mate_wait(const StepArgs& a, int l, int w) {
     // opposite prefix work-groups)
     int im;
     const int rm = wg_role(a, jm, im);
-    const bool one = a.resp_cut == 2;  // each wavefront of a response work-group has a word of its own
-    const bool need = rm == 0 ? im < a.n_prefix_items : rm == 1 ? (one ? im * kWaves + w : im) < a.n_suffix_items : false;
-    const int word = rm == 1 && one ? w : 0;
+    const bool need = rm == 0 ? im < a.n_prefix_items : rm == 1 ? (WAVES ? im * kWaves + w : im) < a.n_suffix_items : false;
+    const int word = rm == 1 && WAVES ? w : 0;
     const int32_t* line = peer_line(a, jm * a.Hkv + g);
     if (need && __hip_atomic_load(line + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == cu_id() + 1) {
       const int32_t target = (int32_t)((uint32_t)a.peer_base + (uint32_t)l + 1u);
@@ -813,7 +715,7 @@ __device__ __forceinline__ void mate_wait(const StepArgs& a, int l, int w) {
   asm volatile("" ::: "memory");
 }
 __device__ void mate_gate(const StepArgs& a, int l) {
-  if (threadIdx.x < 64) mate_wait(a, l, 0);
+  if (threadIdx.x < 64) mate_wait<false>(a, l, 0);
   __syncthreads();
 }
 
@@ -923,7 +825,7 @@ __device__ __forceinline__ void suffix_wave_loop(const StepArgs& a, int g, int i
     const LayerView V = layer_view(a, l);
     if (l > 0 && lane == 0) {
       const int32_t target = (int32_t)((uint32_t)a.merged_base[p] + (uint32_t)l * (uint32_t)a.merged_per_layer[p]);
-      if (!bounded_wait(a, layer_flag(a, p, g), target))
+      if (!bounded_wait(a, layer_flag(a, p, g), target, true))
         __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("" ::: "memory");  // what follows is read after the wait
@@ -963,7 +865,7 @@ __device__ __forceinline__ void suffix_wave_loop(const StepArgs& a, int g, int i
       peer_mark(a, l, w);
     }
     if (l + 1 < a.num_layers) {
-      mate_wait(a, l, w);
+      mate_wait<true>(a, l, w);
       RM::load_round(layer_view(a, l + 1).pool, pages, a.Hkv, g, 0, R);
     }
   }
@@ -982,7 +884,7 @@ __device__ void merge_loop(const StepArgs& a, int g, int mj) {
         const int p = s / a.m;
         const uint32_t per = (uint32_t)(a.slot[s].pieces + a.prompt[p].nchunks);
         const int32_t target = (int32_t)((uint32_t)a.slot[s].target + (uint32_t)(l + 1) * per);
-        merge_wave<SH, L2>(a, V, s, g, target);
+        merge_wave<SH, L2, true>(a, V.o, s, g, target);
         // Counted once this wavefront's partial loads and O stores have completed;
         // the merge that completes the prompt's layer raises every head's flag.
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1007,8 +909,10 @@ __device__ void merge_loop(const StepArgs& a, int g, int mj) {
 }
 
 // The step launch.  Timing mode as in decode_kernel (one start / end pair for
-// the whole launch).
-template <class SH, bool L2>
+// the whole launch).  WAVES: StepArgs::resp_cut == 2; kernels of their own, as
+// both response loops in one kernel cost the other 0.5 % (28 layers, 16 slots up
+// to 1024 tokens: 320.8 against 319.1 us).
+template <class SH, bool L2, bool WAVES>
 __global__ __launch_bounds__(kBlockThreads, SH::MIN_WAVES) void layers_kernel(const StepArgs a) {
   __shared__ __attribute__((aligned(16))) float smem[SH::SMEM > 4 ? SH::SMEM : 4];
   const int cs = (blockIdx.x % kClockSlots) * kClockStride;
@@ -1025,15 +929,13 @@ __global__ __launch_bounds__(kBlockThreads, SH::MIN_WAVES) void layers_kernel(co
   if (role == 0)
     prefix_loop<SH, L2>(a, g, idx, smem);
   else if (role == 1) {
-    bool waves = false;
-    if constexpr (SH::BF) {
-      waves = a.resp_cut == 2;
+    if constexpr (WAVES) {
       const int it = __builtin_amdgcn_readfirstlane(idx * kWaves + (int)(threadIdx.x >> 6));
-      if (waves && it < a.n_suffix_items) suffix_wave_loop<SH, L2>(a, g, it);
+      if (it < a.n_suffix_items) suffix_wave_loop<SH, L2>(a, g, it);
+    } else {
+      suffix_loop<SH, L2>(a, g, idx, smem);
     }
-    if (!waves) suffix_loop<SH, L2>(a, g, idx, smem);
-  }
-  else
+  } else
     merge_loop<SH, L2>(a, g, idx);
   if (a.clock_start) {
     __syncthreads();
@@ -1042,6 +944,11 @@ __global__ __launch_bounds__(kBlockThreads, SH::MIN_WAVES) void layers_kernel(co
                              __HIP_MEMORY_SCOPE_AGENT);
   }
 }
+
+// The kernels of a shape in the order of KernelEntry.
+#define INFS_KERNELS(kernel, ...)                                                                \
+  {kernel<__VA_ARGS__, false, false>, kernel<__VA_ARGS__, true, false>, kernel<__VA_ARGS__, false, (__VA_ARGS__::BF)>, \
+   kernel<__VA_ARGS__, true, (__VA_ARGS__::BF)>}
 
 }  // namespace
 }  // namespace infs

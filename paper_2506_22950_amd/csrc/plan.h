@@ -111,7 +111,8 @@ struct StepArgs {
   int32_t n_pre_wg, n_suf_wg, n_merge_wg;
   int32_t resp_cut;                    // 1: slot s's response items are its slot[s].pieces near-equal page
                                        // ranges (step_plan.h); 0: chunks of `split` tokens; 2: as 1, one item per
-                                       // wavefront (wavefront w of response work-group i takes item 4i + w)
+                                       // wavefront (wavefront w of response work-group i takes item 4i + w).  A per-layer
+                                       // launch: 2 with a response (one item) and a merge per wavefront, else 0
   int32_t merge_j0;                    // first merge work-group of a KV head (>= n_pre_wg)
   int64_t q_layer_stride, kv_layer_stride, o_layer_stride;
   int64_t prefix_layer_bytes, pool_layer_bytes;
