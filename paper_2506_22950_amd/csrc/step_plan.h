@@ -59,7 +59,9 @@ inline int pieces_at(int pages, int scmax, int t, int page_max) {
 // with the largest piece as small as it can be (pieces of at least
 // kPiecePagesMin pages where a response has them).  Writes pieces[s] (0 for an
 // idle slot) and returns the largest piece in pages, or -1 when the slots
-// cannot fit in w pieces.
+// cannot fit in w pieces or a slot's scmax pieces cannot hold it at page_max
+// pages each (chunks of more tokens than that: split_tokens above 1024 with one
+// piece per wavefront).
 inline int cut_responses(const int32_t* len, int S, int w, int scmax, int32_t* pieces, int page_max = kPiecePagesMax) {
   using namespace step_plan_detail;
   auto total = [&](int t) {
@@ -68,6 +70,8 @@ inline int cut_responses(const int32_t* len, int S, int w, int scmax, int32_t* p
       if (len[s] > 0) n += pieces_at(cdiv(len[s], kPageTokens), scmax, t, page_max);
     return n;
   };
+  for (int s = 0; s < S; ++s)
+    if (len[s] > 0 && cdiv(cdiv(len[s], kPageTokens), page_max) > scmax) return -1;
   if (total(page_max) > w) return -1;
   int lo = kPiecePagesMin, hi = page_max;  // smallest t with total(t) <= w
   while (lo < hi) {

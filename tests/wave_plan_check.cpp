@@ -2,7 +2,11 @@
 // csrc/step_plan.h), built with g++ by tests/test_wave_plan.py: over random slot
 // lengths and launch shapes, the roles add up, there is a wavefront for every
 // item, every live response's pieces are whole page ranges that tile it, and
-// pieces stay within the limits per slot and per wavefront.
+// pieces stay within the limits per slot and per wavefront.  Chunk lengths are
+// drawn over the whole accepted range, the pieces a slot has room for as
+// infs_create sizes them: the chunks of the longest response, padded to whole
+// 128-byte lines of records.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -23,9 +27,11 @@ int main() {
   auto uni = [&](int a, int b) { return std::uniform_int_distribution<int>(a, b)(rng); };
   int applied = 0;
   for (int cs = 0; cs < 20000; ++cs) {
-    const int nj = (int[]){2, 3, 8, 32, 63, 64, 128}[uni(0, 6)], S = uni(1, kMaxSlots), split = (int[]){128, 256, 512}[uni(0, 2)];
+    const int nj = (int[]){2, 3, 8, 32, 63, 64, 128}[uni(0, 6)], S = uni(1, kMaxSlots);
+    const int split = uni(0, 1) ? (int[]){128, 256, 512}[uni(0, 2)] : 128 * uni(1, kMaxSplit / 128);
     const int cap = uni(0, 2) ? uni(1, 4096) : uni(1, 20000), idle = uni(0, 3) ? 0 : uni(0, 90);
-    const int scmax = (cap + split - 1) / split, npi = uni(0, 64);
+    const int line = std::max(1, kRecordsPerLine / (1 << uni(0, 3)));  // records of 1, 2, 4, 8 heads per KV head
+    const int scmax = ((cap + split - 1) / split + line - 1) / line * line, npi = uni(0, 64);
     std::vector<int32_t> len(S, 0), pieces(S, -1);
     for (int s = 0; s < S; ++s)
       if (uni(0, 99) >= idle) len[s] = uni(1, cap);
