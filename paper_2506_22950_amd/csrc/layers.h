@@ -260,11 +260,7 @@ struct PrefixTile {
     T::load_q(prefix_query<SH>(a, V.q, it.p, g), q);
     const PrefixRows<SH> ad(a, V.prefix, it.p, g, wt1);
     typename T::Acc A;
-    T::init(A);
-    for (int base = wt0; base < wt1; base += T::TOK) {
-      if (base != wt0) T::load_round(ad, base, R);
-      T::round(R, q, base, wt1, a.scale_log2, A);
-    }
+    T::stored(ad, wt0, wt1, q, a.scale_log2, R, A);
     T::template store<L2>(smem, A, Exchange<L2>(a), (((int64_t)it.p * a.Hkv + g) * a.prefix_chunks_max + it.c) * SH::PR);
     after_stores();
   }
