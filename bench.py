@@ -107,14 +107,16 @@ def mfma_flops(cfg, steplog, split=256, nj=None):
     multiply-add of every 16x16x32 tile issued), every KV head, every layer:
     (prefix) per prompt with a live slot, S^T = K Q^T and O^T = V^T P^T over
     the padded row tile (m * hpk rows padded to 16/32/64/128) and 32-token
-    blocks; (responses, bf16 and E4M3 pages) per live slot, per wavefront of
+    blocks (16 rows and more: the row tiles below weigh V twice, which is not
+    counted); (responses, bf16 and E4M3 pages) per live slot, per wavefront of
     each split-K item, per 32-token page pair of its stored tokens (the newest
     token is folded in apart): two S^T tiles of head_dim / 32 steps, then
     head_dim / 16 O^T tiles and one row-sum tile, each 16 columns wide with hpk
     of them carrying query rows.  The items are the per-layer launch's chunks
     of `split` tokens, or, with nj (work-groups per KV head of a step launch),
     the items the library's step-launch plan gives each step
-    (infs_step_split_plan).  fp32 contexts issue no MFMA."""
+    (infs_step_launch_plan).  bf16 tiles only: fp32 contexts run on fp32 MFMA
+    (16x16x4), which SQ_INSTS_VALU_MFMA_MOPS_BF16 does not count: 0."""
     if cfg.dtype != "bf16":
         return 0.0
     rows = cfg.slots_per_prompt * cfg.hpk
@@ -159,30 +161,28 @@ def mfma_flops(cfg, steplog, split=256, nj=None):
                 ranges.append((w0, min(w0 + ppw * 16, t1)))
         return wave_pairs(length, ranges)
 
+    def single_pairs(length, n):  # near-equal page ranges, one to a wavefront
+        pages = -(-length // 16)
+        return wave_pairs(length, [(c * pages // n * 16, min((c + 1) * pages // n * 16, length)) for c in range(n)])
+
     plan = None
     if nj is not None:
-        from paper_2506_22950_amd import infs
+        from paper_2506_22950_amd.group import context_for
 
-        scmax = -(-cfg.max_suffix_len // split)
-
-        def plan(row):
-            # the library's rule: the per-layer launch's 128-token prefix chunks unless they would
-            # give some producer two items, then 256-token chunks (MFMA tiles, bf16 or E4M3 cache)
-            lens = [e[2] if e is not None else 0 for e in row]
-            live = {e[0] for e in row if e is not None}
-            npi = sum(-(-cfg.prompt_lens[p] // 128) for p in live)
-            r0, _ = infs.step_split_plan(nj, lens, npi, 128, split, scmax, mode=0)
-            psplit = 256 if (r0["items"] > r0["n_suf"] or r0["n_pre"] < npi) else 128
-            npi = sum(-(-cfg.prompt_lens[p] // psplit) for p in live)
-            roles, pieces = infs.step_split_plan(nj, lens, npi, psplit, split, scmax)
-            return roles["cut"], pieces
+        plan = context_for(cfg, dry_run=True, split_tokens=split)
+        for p, plen in enumerate(cfg.prompt_lens):
+            plan.prefill_shared(p, 0, plen, None, None)
 
     total = 0
     for row in steplog:
         total += sum(per_prompt[p] for p in {e[0] for e in row if e is not None})
-        cut, pieces = plan(row) if plan is not None else (0, None)
+        cut = 0
+        if plan is not None:
+            roles, pieces = plan.step_launch_plan([e[2] if e is not None else 0 for e in row], nj)
+            cut = roles["cut"]
         if cut:
-            n = sum(piece_pairs(e[2], int(pieces[s])) for s, e in enumerate(row) if e is not None)
+            count = single_pairs if cut == 2 else piece_pairs
+            n = sum(count(e[2], int(pieces[s])) for s, e in enumerate(row) if e is not None)
         else:
             n = sum(pairs(e[2]) for e in row if e is not None)
         total += n * per_pair * cfg.num_kv_heads

@@ -342,8 +342,8 @@ infs_status infs_set_exchange(infs_ctx* ctx, int32_t mode);
    prefix in chunks of 256 tokens on MFMA tiles, bf16 or E4M3 cache (two per-layer chunks, walked by
    the same work-group), which leaves more work-groups for the responses.
    With more than 32 slots and many chunks (bf16 Q/K/V), mode 1 gives every wavefront of a response
-   work-group a response piece of its own instead, with fewer merge work-groups; infs_step_split_plan does
-   not describe this split.
+   work-group a response piece of its own instead, with fewer merge work-groups (infs_step_launch_plan
+   tells which split a step gets).
    mode 0: responses in chunks of split_tokens, the prefix in the per-layer launch's chunks, and
            work-groups divided in proportion to the chunk counts, the partition of infs_decode_step:
            outputs then differ from a per-layer decode only in the order the merges add partials.
@@ -351,7 +351,8 @@ infs_status infs_set_exchange(infs_ctx* ctx, int32_t mode);
    mode; E_STATE while a step is open. */
 infs_status infs_set_step_split(infs_ctx* ctx, int32_t mode);
 
-/* The work split a step launch in `mode` (as infs_set_step_split) uses for one step, with nj
+/* The work split a step launch in `mode` (as infs_set_step_split) uses for one step whose response
+   pieces go to work-groups (not one to a wavefront: infs_step_launch_plan gives that split too), with nj
    work-groups per KV head (infs_step_launch_workgroups / num_kv_heads), S slots of which slot s holds
    len[s] tokens (0 = idle), n_prefix_items prefix chunks of prefix_split tokens (a step launch in mode 1
    takes the prefix in chunks of 128 tokens on MFMA tiles, or of 256 where the
@@ -366,6 +367,18 @@ infs_status infs_set_step_split(infs_ctx* ctx, int32_t mode);
 infs_status infs_step_split_plan(int32_t nj, int32_t S, int32_t n_prefix_items, int32_t prefix_split,
                                  const int32_t* len, int32_t split, int32_t scmax, int32_t mode, int32_t* pieces,
                                  int32_t* roles);
+
+/* The work split an infs_decode_step_layers launch of this context uses, in the mode set, for a step in
+   which slot s holds len[s] tokens with the new one (0 = idle; len has num_prompts * slots_per_prompt
+   entries), with nj work-groups per KV head (0: those of this context's device).  Writes pieces[s]
+   (response items per slot) and roles[0..7) = {prefix work-groups, response work-groups, merge
+   work-groups, response items, cut, prefix chunks, tokens of a prefix chunk}; cut 0: responses in chunks
+   of split_tokens, 1: in near-equal page ranges, one to a work-group, 2: in near-equal page ranges, one
+   to a wavefront.  Changes nothing; for diagnostics and tests, dry-run contexts answer too (with nj).
+   E_ARG: null pointers, fewer than 2 work-groups, a len outside [0, max_suffix_len]; E_STATE: a live
+   slot's prompt has no prefix. */
+infs_status infs_step_launch_plan(const infs_ctx* ctx, int32_t nj, const int32_t* len, int32_t* pieces,
+                                  int32_t* roles);
 
 /* The current exchange mode (0, 1 or 2); -1 for a NULL context. */
 int32_t infs_exchange_mode(const infs_ctx* ctx);

@@ -854,6 +854,33 @@ infs_status infs_release_sample(infs_ctx* c, int32_t prompt, int64_t sample_id) 
 
 namespace {
 
+// Tokens of a step launch's prefix chunks when the per-layer launch's chunks are
+// n_prefix_items: MFMA prefix chunks of kStepPrefixSplit tokens (bf16 or E4M3
+// cache) when the per-layer chunks would give some producer two items: half as
+// many prefix work-groups, each walking twice the blocks with the next block in
+// flight, leave more work-groups to the responses (the records of 128-token
+// chunks have room for them).
+int launch_prefix_split(const infs_ctx* c, int nj, int n_prefix_items, const int32_t* lens) {
+  return c->step_split && c->key.mfma && infs::longer_prefix_chunks(nj, c->S, n_prefix_items, lens, c->split)
+             ? infs::kStepPrefixSplit
+             : c->prefix_split;
+}
+
+// Work-groups per KV head of a step launch by role (merges, prefix chunks and
+// response pieces, so that no producer reads many more tokens than the others)
+// and the response pieces of every slot.  Returns StepArgs::resp_cut.
+int plan_split(const infs_ctx* c, const KernelKey& key, int nj, int S, int prompts, int n_prefix_items, int prefix_split,
+               const int32_t* lens, int32_t* pieces, infs::StepRoles* roles) {
+  if (c->step_split == 0) {
+    *roles = infs::plan_step_roles_chunks(nj, S, n_prefix_items, lens, c->split, pieces);
+    return 0;
+  }
+  if (key.bf16 && infs::plan_step_waves(nj, S, prompts, n_prefix_items, prefix_split, lens, c->split, c->scmax, pieces, roles))
+    return 2;
+  *roles = infs::plan_step_roles(nj, S, n_prefix_items, prefix_split, lens, c->split, c->scmax, pieces);
+  return roles->cut ? 1 : 0;
+}
+
 // Roles, counter targets and launch of a step launch through every layer of
 // plan `a` (a decode step or a probe step) with nj work-groups per KV head.
 // slot_arrivals[s] and merged_arrivals[p] are the host's running values of the
@@ -863,18 +890,10 @@ infs_status launch_step_layers(infs_ctx* c, const KernelKey& key, StepArgs& a, i
                                uint32_t* merged_arrivals) {
   a.peer = peer_lines(c);
   a.peer_base = (int32_t)c->peer_progress;
-  // Work-groups per KV head: one merge wavefront per slot, the rest split between prefix chunks
-  // and response pieces so that no producer reads many more tokens than the others.
   int32_t lens[infs::kMaxSlots], pieces[infs::kMaxSlots];
   for (int s = 0; s < a.S; ++s) lens[s] = a.slot[s].len;
   infs::StepRoles roles;
-  const bool waves = c->step_split && key.bf16 &&
-                     infs::plan_step_waves(nj, a.S, a.num_prompts, a.n_prefix_items, a.prefix_split, lens, c->split,
-                                           c->scmax, pieces, &roles);
-  if (!waves)
-    roles = c->step_split ? infs::plan_step_roles(nj, a.S, a.n_prefix_items, a.prefix_split, lens, c->split, c->scmax,
-                                                  pieces)
-                          : infs::plan_step_roles_chunks(nj, a.S, a.n_prefix_items, lens, c->split, pieces);
+  const int cut = plan_split(c, key, nj, a.S, a.num_prompts, a.n_prefix_items, a.prefix_split, lens, pieces, &roles);
   if ((a.n_prefix_items > 0 && roles.n_pre < 1) || (roles.n_suffix_items > 0 && roles.n_suf < 1))
     return fail(c, INFS_E_STATE, "no step launch on this device: %d work-groups per KV head cannot take prefix "
                 "chunks, response chunks and merges", nj);
@@ -887,7 +906,7 @@ infs_status launch_step_layers(infs_ctx* c, const KernelKey& key, StepArgs& a, i
     items += pieces[s];
   }
   a.n_suffix_items = roles.n_suffix_items;
-  a.resp_cut = waves ? 2 : roles.cut ? 1 : 0;
+  a.resp_cut = cut;
   // Merges go opposite the prefix work-groups (index j shares its CU with j + nj/2, see
   // mate_gate), else after the response work-groups.
   a.merge_j0 = (nj % 2 == 0 && a.n_pre_wg <= nj / 2 && a.n_merge_wg <= nj / 2) ? nj / 2 : a.n_pre_wg + a.n_suf_wg;
@@ -1048,13 +1067,9 @@ infs_status infs_decode_step_layers(infs_ctx* c, const void* q_dev, const void* 
     a.merged = merged_counters(c);
     int32_t lens[infs::kMaxSlots];
     for (int s = 0; s < c->S; ++s) lens[s] = a.slot[s].len;
-    if (c->step_split && c->key.mfma &&
-        infs::longer_prefix_chunks(c->layers_resident / c->Hkv, c->S, a.n_prefix_items, lens, c->split)) {
-      // MFMA prefix chunks of kStepPrefixSplit tokens (bf16 or E4M3 cache) when the per-layer
-      // chunks would give some producer two items: half as many prefix work-groups, each walking
-      // twice the blocks with the next block in flight, leave more work-groups to the responses
-      // (the records of 128-token chunks have room for them).
-      a.prefix_split = infs::kStepPrefixSplit;
+    const int psplit = launch_prefix_split(c, c->layers_resident / c->Hkv, a.n_prefix_items, lens);
+    if (psplit != a.prefix_split) {
+      a.prefix_split = psplit;
       int items = 0;
       for (int p = 0; p < c->NP; ++p) {
         infs::PromptPlan& pp = a.prompt[p];
@@ -1274,6 +1289,37 @@ infs_status infs_step_split_plan(int32_t nj, int32_t S, int32_t n_prefix_items, 
   roles[2] = r.n_merge;
   roles[3] = r.n_suffix_items;
   roles[4] = r.cut ? 1 : 0;
+  return INFS_OK;
+}
+
+infs_status infs_step_launch_plan(const infs_ctx* c, int32_t nj, const int32_t* len, int32_t* pieces, int32_t* roles) {
+  if (!c) return fail(nullptr, INFS_E_ARG, "null context");
+  infs_ctx* cc = const_cast<infs_ctx*>(c);  // for the message of a failed call
+  if (!len || !pieces || !roles) return fail(cc, INFS_E_ARG, "step_launch_plan: null array");
+  if (nj == 0) nj = c->layers_resident / c->Hkv;
+  if (nj < 2) return fail(cc, INFS_E_ARG, "step_launch_plan: a step launch needs 2 work-groups per KV head, not %d", nj);
+  std::vector<bool> live(c->NP, false);
+  for (int s = 0; s < c->S; ++s) {
+    if (len[s] < 0 || len[s] > c->cfg.max_suffix_len)
+      return fail(cc, INFS_E_ARG, "step_launch_plan: len[%d] = %d outside [0, %d]", s, len[s], c->cfg.max_suffix_len);
+    if (len[s] > 0) live[s / c->m] = true;
+  }
+  for (int p = 0; p < c->NP; ++p)
+    if (live[p] && c->plen[p] < 0) return fail(cc, INFS_E_STATE, "prompt %d has live slots but no prefilled prefix", p);
+  auto items = [&](int split) {
+    int n = 0;
+    for (int p = 0; p < c->NP; ++p) n += live[p] ? ceil_div(c->plen[p], split) : 0;
+    return n;
+  };
+  const int psplit = launch_prefix_split(c, nj, items(c->prefix_split), len);
+  infs::StepRoles r;
+  roles[4] = plan_split(c, c->key, nj, c->S, c->NP, items(psplit), psplit, len, pieces, &r);
+  roles[0] = r.n_pre;
+  roles[1] = r.n_suf;
+  roles[2] = r.n_merge;
+  roles[3] = r.n_suffix_items;
+  roles[5] = items(psplit);
+  roles[6] = psplit;
   return INFS_OK;
 }
 

@@ -39,7 +39,7 @@ EXPORTS = (
     "infs_probe_state", "infs_release_sample", "infs_read_prefix", "infs_read_response", "infs_set_merge_wait",
     "infs_get_kernel_info", "infs_set_exchange", "infs_exchange_mode", "infs_decode_step_static",
     "infs_sched_optimum", "infs_decode_step_layers", "infs_step_launch_workgroups", "infs_set_step_split",
-    "infs_step_split_plan", "infs_probe_step_layers",
+    "infs_step_split_plan", "infs_step_launch_plan", "infs_probe_step_layers",
 )
 
 
@@ -105,6 +105,7 @@ def load():
         "infs_set_step_split": (I32, [P, I32]),
         "infs_step_split_plan": (I32, [I32, I32, I32, I32, ctypes.POINTER(I32), I32, I32, I32, ctypes.POINTER(I32),
                                        ctypes.POINTER(I32)]),
+        "infs_step_launch_plan": (I32, [P, I32, ctypes.POINTER(I32), ctypes.POINTER(I32), ctypes.POINTER(I32)]),
         "infs_timing_begin": (I32, [P]),
         "infs_timing_end": (I32, [P, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double),
                                   ctypes.POINTER(I64)]),
@@ -211,6 +212,19 @@ class Context:
     def decode_step_layers(self, q, k_new, v_new, o, q_layer_stride=0, kv_layer_stride=0, o_layer_stride=0):
         self._call(load().infs_decode_step_layers, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(o), q_layer_stride,
                    kv_layer_stride, o_layer_stride)
+
+    def step_launch_plan(self, lens, nj=0):
+        """infs_step_launch_plan: (roles, pieces) of a step launch over slots of lens[s] tokens, roles =
+        dict(n_pre, n_suf, n_merge, items, cut, prefix_items, prefix_split)."""
+        L = np.ascontiguousarray(lens, dtype=np.int32)
+        if len(L) != self.config.num_prompts * self.config.slots_per_prompt:
+            raise ValueError("one length per slot")
+        pieces, roles = np.zeros(len(L), dtype=np.int32), np.zeros(7, dtype=np.int32)
+        I32P = ctypes.POINTER(ctypes.c_int32)
+        self._call(load().infs_step_launch_plan, nj, L.ctypes.data_as(I32P), pieces.ctypes.data_as(I32P),
+                   roles.ctypes.data_as(I32P))
+        return dict(zip(("n_pre", "n_suf", "n_merge", "items", "cut", "prefix_items", "prefix_split"),
+                        (int(x) for x in roles))), pieces
 
     @property
     def step_launch_workgroups(self):

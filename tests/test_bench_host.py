@@ -51,7 +51,7 @@ def test_mfma_flops_closed_form():
     # (299 minus 256, the newest apart) on the next chunk's first wavefront (2 pairs): 10 pairs
     long = [[(0, 0, 300)] + [None] * 15]
     assert bench.mfma_flops(big, long) - bench.mfma_flops(big, one) == 28 * 10 * pair
-    assert bench.mfma_flops(get_config("tiny_f32"), log) == 0  # fp32 contexts issue no MFMA
+    assert bench.mfma_flops(get_config("tiny_f32"), log) == 0  # fp32 contexts issue no bf16 MFMA
     # Step launch with 64 work-groups per KV head (8 prefix chunks of 256 tokens): one 300-token
     # response fits the chunks, so the count is the same.  Sixteen of 900 tokens (57 pages) are 64
     # chunks for the chunk plan's 54 response work-groups, so the plan keeps 8 prefix work-groups
@@ -61,6 +61,28 @@ def test_mfma_flops_closed_form():
     assert bench.mfma_flops(big, long, nj=64) == bench.mfma_flops(big, long)
     many = [[(0, i, 900) for i in range(16)]]
     assert bench.mfma_flops(big, many, nj=64) - bench.mfma_flops(big, many) == 28 * 16 * 4 * pair
+
+
+def test_mfma_flops_of_wavefront_pieces():
+    # 64 slots on four prompts (hpk 4, d=128, 8 KV heads), 64 work-groups per KV head, every response
+    # 500 tokens (32 pages, 499 stored): the step launch cuts responses into one piece per wavefront.
+    cfg = get_config("qwen3_8b_4prompts").with_(layers=3)
+    log = [[(s // 16, s % 16, 500) for s in range(64)]]
+    from paper_2506_22950_amd.group import context_for
+    ctx = context_for(cfg, dry_run=True)
+    for p, plen in enumerate(cfg.prompt_lens):
+        ctx.prefill_shared(p, 0, plen, None, None)
+    roles, pieces = ctx.step_launch_plan([500] * 64, 64)
+    assert roles["cut"] == 2 and set(pieces) == {pieces[0]}  # equal responses, equal cuts
+    n = int(pieces[0])
+    tile = 2 * 16 * 16 * 32
+    pair = (2 * 4 + 8 + 1) * tile
+    pairs = 0
+    for c in range(n):  # page range of piece c; the newest token (499) is folded in apart
+        t0, t1 = c * 32 // n * 16, min((c + 1) * 32 // n * 16, 499)
+        pairs += (t1 - t0 + 31) // 32
+    prefix = 4 * 64 * sum(-(-p // 32) * 32 for p in cfg.prompt_lens) * 128
+    assert bench.mfma_flops(cfg, log, nj=64) == 3 * 8 * (prefix + 64 * pairs * pair)
 
 
 def test_launches_per_entry():

@@ -21,7 +21,8 @@ pytestmark = pytest.mark.sanitize
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SUITES = ["tests/test_abi_host.py", "tests/test_state_machine.py", "tests/test_c_consumer.py",
-          "tests/test_step_plan.py::test_step_split_plan_hand_cases"]
+          "tests/test_step_plan.py::test_step_split_plan_hand_cases",
+          "tests/test_step_plan.py::test_step_launch_plan_is_the_launch_rule"]
 
 
 def test_host_runtime_under_asan_and_ubsan():

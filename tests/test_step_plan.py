@@ -63,3 +63,33 @@ def test_step_split_plan_hand_cases():
         infs.step_split_plan(64, [5000], 1, 128, 256, 16)   # longer than scmax * split
     with pytest.raises(infs.InfsError):
         infs.step_split_plan(1, [5], 1, 128, 256, 16)
+
+
+def test_step_launch_plan_is_the_launch_rule():
+    # Through the C ABI, on a dry-run context: the split by work-groups as infs_step_split_plan tells
+    # it, and one piece per wavefront where the step launch takes that; arguments are checked.
+    from paper_2506_22950_amd import infs
+    cfg = infs.make_config(num_layers=2, num_q_heads=16, num_kv_heads=8, head_dim=128, num_prompts=1,
+                           slots_per_prompt=64, samples_per_prompt=64, max_prompt_len=2048, max_suffix_len=4096,
+                           dtype=infs.BF16, flags=infs.FLAG_DRY_RUN)
+    ctx = infs.Context(cfg)
+    with pytest.raises(infs.InfsError):
+        ctx.step_launch_plan([0, 5] + [0] * 62, 64)  # no prefix yet
+    ctx.prefill_shared(0, 0, 1024, None, None)
+    few = [300] * 16 + [0] * 48
+    roles, pieces = ctx.step_launch_plan(few, 64)
+    want, wp = infs.step_split_plan(64, few, roles["prefix_items"], roles["prefix_split"], 256, 16)
+    assert {k: roles[k] for k in want} == want and list(pieces) == list(wp)
+    assert (roles["prefix_items"], roles["prefix_split"]) in ((8, 128), (4, 256))
+    many = [1000] * 64
+    roles, pieces = ctx.step_launch_plan(many, 64)
+    assert roles["cut"] == 2 and roles["items"] == pieces.sum() <= 4 * roles["n_suf"]
+    assert roles["n_pre"] + roles["n_suf"] + roles["n_merge"] == 64
+    ctx.set_step_split(0)
+    roles, pieces = ctx.step_launch_plan(many, 64)
+    assert roles["cut"] == 0 and roles["prefix_split"] == 128 and list(pieces) == [4] * 64
+    for bad in ((many, 1), (many, 0), ([4097] + [0] * 63, 64), ([-1] + [0] * 63, 64)):
+        with pytest.raises(infs.InfsError):
+            ctx.step_launch_plan(*bad)
+    assert ctx.get_stats().steps == 0
+    ctx.destroy()
