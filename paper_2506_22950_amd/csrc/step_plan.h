@@ -131,69 +131,6 @@ inline bool longer_prefix_chunks(int nj, int S, int n_prefix_items, const int32_
   return r.n_suffix_items > r.n_suf || r.n_pre < n_prefix_items;
 }
 
-// The split of a step with one response piece per wavefront (bf16 and E4M3
-// pages): the four wavefronts of a response work-group take a piece each, of
-// whichever slots, and hand in a partial each, without a barrier or a combine
-// between them.  With many slots the work-group pieces of plan_step_roles are
-// dealt several to a work-group, each loaded, combined and counted in turn;
-// here every wavefront has one.  The price is four times the partials, which
-// few slots with long responses pay in their merges.  Measured before and with
-// it, us a step; 36 layers, 4 prompts (256 to 4096 tokens), 32/8 heads: 64 slots
-// of responses up to 256 tokens 1179 and 835, up to 1024 tokens 1804 and 1353,
-// up to 2048 tokens 2749 and 2308; 48 slots up to 700 tokens 1422 and 977; 36
-// slots up to 700 tokens 985 and 844.  One prompt of 1024 tokens, 28 layers, 16/8
-// heads: 64 slots up to 1000 tokens 1011 and 837, 40 slots up to 1500 tokens 1049
-// and 778; but 32 slots up to 2048 tokens 860 and 923, 16 slots up to 2048 tokens
-// 472 and 621, and with few per-layer chunks to a response work-group 64 slots
-// up to 300 tokens (1.6 chunks) 697 and 716, 40 slots up to 600 tokens (1.3) 611
-// and 678.  Hence more than kWaveMinSlots slots and kWaveMinItems4 / 4 chunks.
-//
-// A merge work-group only waits while the others load, so the merges run on
-// fewer than one wavefront each: two to a wavefront, and four where several
-// prompts walk the layers on their own, unless the responses are deep
-// (kWaveDeepItems chunks and more).  One, two, four merges to a wavefront: one
-// prompt, 64 slots up to 1000 tokens 1114, 837, 913; 4 prompts, 64 slots up to
-// 512 tokens 1142, 1203, 961, up to 2048 tokens 2534, 2243, 2450.
-// The prefix is weighed kWavePrefixCost halves, as its chunks are walked after
-// the layer's queries arrive.
-// False where it does not apply: few slots or chunks, or pieces that would not
-// fit a wavefront.
-constexpr int kWaveMinSlots = 32, kWaveMinItems4 = 7, kWaveDeepItems = 5, kWavePrefixCost = 3;
-constexpr int kWavePagesMax = 64;  // a wavefront holds the page numbers of its piece one per lane
-inline bool plan_step_waves(int nj, int S, int prompts, int n_prefix_items, int prefix_split, const int32_t* len, int split, int scmax,
-                            int32_t* pieces, StepRoles* out) {
-  using namespace step_plan_detail;
-  StepRoles r = plan_step_roles_chunks(nj, S, n_prefix_items, len, split, pieces);
-  if (S <= kWaveMinSlots || 4 * r.n_suffix_items < kWaveMinItems4 * r.n_suf) return false;
-  const int merges = prompts > 1 && r.n_suffix_items < kWaveDeepItems * r.n_suf ? 4 : 2;  // to a wavefront
-  r.n_merge = cdiv(S, merges * kWaves) < nj - 1 ? cdiv(S, merges * kWaves) : nj - 1;
-  const int prod = nj - r.n_merge;
-  int best = -1, best_pre = 0;
-  const int kmax = n_prefix_items > 0 ? n_prefix_items : 1;
-  for (int k = 1; k <= kmax; ++k) {
-    const int n_pre = n_prefix_items > 0 ? cdiv(n_prefix_items, k) : 0;
-    const int w = prod - n_pre;
-    if (w < 1) continue;
-    const int big = cut_responses(len, S, w * kWaves, scmax, pieces, kWavePagesMax);
-    if (big <= 0) continue;
-    const int pre_tokens = kWavePrefixCost * k * prefix_split / 2, resp_tokens = big * kPageTokens * kWaves;
-    const int cost = pre_tokens > resp_tokens ? pre_tokens : resp_tokens;
-    if (best < 0 || cost < best) {
-      best = cost;
-      best_pre = n_pre;
-    }
-  }
-  if (best < 0) return false;
-  r.n_pre = best_pre;
-  r.n_suf = prod - best_pre;
-  cut_responses(len, S, r.n_suf * kWaves, scmax, pieces, kWavePagesMax);
-  r.cut = true;
-  r.n_suffix_items = 0;
-  for (int s = 0; s < S; ++s) r.n_suffix_items += pieces[s];
-  *out = r;
-  return true;
-}
-
 // Roles of the nj work-groups per KV head and the response pieces of a step.
 // n_prefix_items prefix chunks of prefix_split tokens; live slot s has len[s]
 // tokens; the per-layer launch cuts responses into chunks of `split` tokens,
@@ -244,6 +181,109 @@ inline StepRoles plan_step_roles(int nj, int S, int n_prefix_items, int prefix_s
   r.n_suffix_items = 0;
   for (int s = 0; s < S; ++s) r.n_suffix_items += pieces[s];
   return r;
+}
+
+// Most tokens the plan deals to one response work-group of a KV head (0 < n_suf <
+// 2 * kMaxSlots of them; work-group i takes items i, i + n_suf, ... of the slots'
+// pieces in order).
+inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, int split, const int32_t* pieces) {
+  int32_t tokens[2 * kMaxSlots] = {};
+  int it = 0, most = 0;
+  for (int s = 0; s < S; ++s) {
+    const int pages = step_plan_detail::cdiv(len[s], kPageTokens);
+    for (int c = 0; c < pieces[s]; ++c, ++it) {
+      int32_t& t = tokens[it % r.n_suf];
+      t += r.cut ? (piece_first_page(c + 1, pages, pieces[s]) - piece_first_page(c, pages, pieces[s])) * kPageTokens
+                 : len[s] - c * split < split ? len[s] - c * split : split;
+      if (t > most) most = t;
+    }
+  }
+  return most;
+}
+
+// The split of a step with one response piece per wavefront (bf16 and E4M3
+// pages): the four wavefronts of a response work-group take a piece each, of
+// whichever slots, and hand in a partial each, without a barrier or a combine
+// between them.  With many slots the work-group pieces of plan_step_roles are
+// dealt several to a work-group, each loaded, combined and counted in turn;
+// here every wavefront has one.  The price is more partials, which the merges
+// pay.  It is taken where all of these hold (us a step of 12 layers, without and
+// with it, 32/8 heads of 128 on four prompts of 256 to 4096 tokens or 16/8 heads
+// on one of 1024, unless said otherwise):
+// * Four times its largest piece, what a work-group then reads, is no more than
+//   plan_step_roles deals to a work-group.  Four prompts, 64 slots up to 256
+//   tokens 404 and 288, up to 700 tokens 499 and 404, up to 2048 tokens 934 and
+//   777, 24 of the 64 live 411 and 332; one prompt, 64 slots up to 1000 tokens
+//   437 and 362; head size 64, up to 2000 tokens 583 and 381; 8 heads per KV
+//   head, up to 1000 tokens 542 and 458.  Past the line: 16 live of 64 up to 700
+//   tokens 255 and 265, one prompt, 24 live up to 2000 tokens 258 and 276, 8 heads
+//   per KV head, 32 live up to 1000 tokens 376 and 397.
+// * kWaveMinItems4 / 4 per-layer chunks to a response work-group and more: one
+//   prompt, 64 slots up to 300 tokens (1.6) 298 and 308, 48 live (1.2) 274 and
+//   301; at the line 48 live up to 700 tokens 295 and 305, but four prompts,
+//   64 slots up to 256 tokens (1.9) the 404 and 288 above.
+// * More than kWaveMinSlots slots, and more than half as many as work-groups per
+//   KV head.  The merge work-groups it frees are few with fewer: 32 slots up to
+//   2048 tokens (28 layers) 860 and 923, 16 slots 472 and 621.  With 4 KV heads
+//   (128 work-groups) plan_step_roles has a work-group for every slot: 64 slots up
+//   to 4000 tokens on two prompts 680 and 812, on one 663 and 594, up to 6000
+//   tokens 996 and 947, 48 live 716 and 752; 2 KV heads up to 9000 tokens (6
+//   layers) 334 and 371.
+// * Not E4M3 pages under a 128-row prefix tile (the caller's check): one prompt of
+//   2048, 64 slots up to 500 tokens 314 and 323, up to 1000 tokens 371 and 530, up
+//   to 2000 tokens 560 and 605.  Under 64 rows and fewer: four prompts, up to 256
+//   tokens 346 and 264, up to 2048 tokens 617 and 596, 16 rows up to 1500 tokens
+//   473 and 295.
+//
+// A merge work-group only waits while the others load, so the merges run on
+// fewer than one wavefront each: two to a wavefront, and four where more than two
+// prompts walk the layers on their own, unless the responses are deep
+// (kWaveDeepItems chunks and more).  Their number follows the slots, not the live
+// ones: 16 of 64 live up to 256 tokens 231 and 296 with fewer.  One, two, four
+// merges to a wavefront: one prompt, 64 slots up to 1000 tokens (28 layers) 1114,
+// 837, 913; two prompts up to 500 tokens 233, 222, 243 (E4M3 202, 204, 252), up to
+// 1500 tokens 543, 504, 485; three up to 1000 tokens 376, 348, 345; 4 prompts (36
+// layers) up to 512 tokens 1142, 1203, 961, up to 2048 tokens 2534, 2243, 2450.
+// The prefix is weighed kWavePrefixCost halves, as its chunks are walked after
+// the layer's queries arrive.
+// False where it does not apply, or where pieces would not fit a wavefront.
+constexpr int kWaveMinSlots = 32, kWaveMinItems4 = 7, kWaveDeepItems = 5, kWavePrefixCost = 3;
+constexpr int kWavePagesMax = 64;  // a wavefront holds the page numbers of its piece one per lane
+inline bool plan_step_waves(int nj, int S, int prompts, int n_prefix_items, int prefix_split, const int32_t* len, int split, int scmax,
+                            int32_t* pieces, StepRoles* out) {
+  using namespace step_plan_detail;
+  StepRoles r = plan_step_roles_chunks(nj, S, n_prefix_items, len, split, pieces);
+  if (S <= kWaveMinSlots || 2 * S <= nj || 4 * r.n_suffix_items < kWaveMinItems4 * r.n_suf) return false;
+  const int merges = prompts > 2 && r.n_suffix_items < kWaveDeepItems * r.n_suf ? 4 : 2;  // to a wavefront
+  r.n_merge = cdiv(S, merges * kWaves) < nj - 1 ? cdiv(S, merges * kWaves) : nj - 1;
+  const int prod = nj - r.n_merge;
+  int best = -1, best_pre = 0;
+  const int kmax = n_prefix_items > 0 ? n_prefix_items : 1;
+  for (int k = 1; k <= kmax; ++k) {
+    const int n_pre = n_prefix_items > 0 ? cdiv(n_prefix_items, k) : 0;
+    if (k > 1 && n_pre == cdiv(n_prefix_items, k - 1)) continue;
+    const int w = prod - n_pre;
+    if (w < 1) continue;
+    const int big = cut_responses(len, S, w * kWaves, scmax, pieces, kWavePagesMax);
+    if (big <= 0) continue;
+    const int pre_tokens = kWavePrefixCost * k * prefix_split / 2, resp_tokens = big * kPageTokens * kWaves;
+    const int cost = pre_tokens > resp_tokens ? pre_tokens : resp_tokens;
+    if (best < 0 || cost < best) {
+      best = cost;
+      best_pre = n_pre;
+    }
+  }
+  if (best < 0) return false;
+  r.n_pre = best_pre;
+  r.n_suf = prod - best_pre;
+  const StepRoles groups = plan_step_roles(nj, S, n_prefix_items, prefix_split, len, split, scmax, pieces);
+  const int dealt = groups.n_suf > 0 ? most_response_tokens(groups, S, len, split, pieces) : 0;
+  if (cut_responses(len, S, r.n_suf * kWaves, scmax, pieces, kWavePagesMax) * kPageTokens * kWaves > dealt) return false;
+  r.cut = true;
+  r.n_suffix_items = 0;
+  for (int s = 0; s < S; ++s) r.n_suffix_items += pieces[s];
+  *out = r;
+  return true;
 }
 
 }  // namespace infs

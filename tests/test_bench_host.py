@@ -64,25 +64,28 @@ def test_mfma_flops_closed_form():
 
 
 def test_mfma_flops_of_wavefront_pieces():
-    # 64 slots on four prompts (hpk 4, d=128, 8 KV heads), 64 work-groups per KV head, every response
-    # 500 tokens (32 pages, 499 stored): the step launch cuts responses into one piece per wavefront.
-    cfg = get_config("qwen3_8b_4prompts").with_(layers=3)
-    log = [[(s // 16, s % 16, 500) for s in range(64)]]
+    # 64 slots on four prompts (hpk 4, d=128, 8 KV heads), 64 work-groups per KV head, responses of 40 to
+    # 670 tokens: the step launch cuts them into one piece per wavefront.
     from paper_2506_22950_amd.group import context_for
+
+    cfg = get_config("qwen3_8b_4prompts").with_(layers=3)
+    lens = [40 + 10 * (s * 29 % 64) for s in range(64)]
     ctx = context_for(cfg, dry_run=True)
     for p, plen in enumerate(cfg.prompt_lens):
         ctx.prefill_shared(p, 0, plen, None, None)
-    roles, pieces = ctx.step_launch_plan([500] * 64, 64)
-    assert roles["cut"] == 2 and set(pieces) == {pieces[0]}  # equal responses, equal cuts
-    n = int(pieces[0])
+    roles, pieces = ctx.step_launch_plan(lens, 64)
+    ctx.destroy()
+    assert roles["cut"] == 2 and max(pieces) > 1
     tile = 2 * 16 * 16 * 32
     pair = (2 * 4 + 8 + 1) * tile
     pairs = 0
-    for c in range(n):  # page range of piece c; the newest token (499) is folded in apart
-        t0, t1 = c * 32 // n * 16, min((c + 1) * 32 // n * 16, 499)
-        pairs += (t1 - t0 + 31) // 32
+    for n, length in zip(pieces.tolist(), lens):
+        pages = -(-length // 16)
+        for c in range(n):  # page range of piece c; the newest token is folded in apart
+            t0, t1 = c * pages // n * 16, min((c + 1) * pages // n * 16, length - 1)
+            pairs += max(0, t1 - t0 + 31) // 32
     prefix = 4 * 64 * sum(-(-p // 32) * 32 for p in cfg.prompt_lens) * 128
-    assert bench.mfma_flops(cfg, log, nj=64) == 3 * 8 * (prefix + 64 * pairs * pair)
+    assert bench.mfma_flops(cfg, [[(s // 16, s % 16, n) for s, n in enumerate(lens)]], nj=64) == 3 * 8 * (prefix + pairs * pair)
 
 
 def test_launches_per_entry():

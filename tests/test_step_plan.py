@@ -85,6 +85,7 @@ def test_step_launch_plan_is_the_launch_rule():
     roles, pieces = ctx.step_launch_plan(many, 64)
     assert roles["cut"] == 2 and roles["items"] == pieces.sum() <= 4 * roles["n_suf"]
     assert roles["n_pre"] + roles["n_suf"] + roles["n_merge"] == 64
+    assert ctx.step_launch_plan(many, 128)[0]["cut"] == 1  # a work-group for every slot
     ctx.set_step_split(0)
     roles, pieces = ctx.step_launch_plan(many, 64)
     assert roles["cut"] == 0 and roles["prefix_split"] == 128 and list(pieces) == [4] * 64
@@ -92,4 +93,30 @@ def test_step_launch_plan_is_the_launch_rule():
         with pytest.raises(infs.InfsError):
             ctx.step_launch_plan(*bad)
     assert ctx.get_stats().steps == 0
+    ctx.destroy()
+    # 24 of 64 slots live, up to 2000 tokens (at most 8 pieces each): a work-group of the split by
+    # work-groups reads less than four wavefronts with a piece each would
+    cfg.max_suffix_len = 2000
+    ctx = infs.Context(cfg)
+    ctx.prefill_shared(0, 0, 1024, None, None)
+    few = [0] * 64
+    for i in range(24):
+        few[i * 64 // 24] = 83 * (i + 1)
+    assert ctx.step_launch_plan(few, 64)[0]["cut"] == 1
+    assert ctx.step_launch_plan([31 * (s + 1) for s in range(64)], 64)[0]["cut"] == 2
+    ctx.destroy()
+
+
+@pytest.mark.parametrize("hpk,prompts,fp8,cut", [(2, 1, False, 2), (2, 1, True, 0), (1, 1, True, 2), (4, 2, True, 0),
+                                                 (4, 4, True, 2)])
+def test_e4m3_pages_take_wavefront_pieces_up_to_64_rows(hpk, prompts, fp8, cut):
+    # 64 slots: one to four prompts, 64 or 128 rows of a prefix tile
+    from paper_2506_22950_amd import infs
+    ctx = infs.Context(infs.make_config(
+        num_layers=1, num_q_heads=8 * hpk, num_kv_heads=8, head_dim=128, num_prompts=prompts, slots_per_prompt=64 // prompts,
+        samples_per_prompt=64, max_prompt_len=2048, max_suffix_len=2000, dtype=infs.BF16,
+        flags=infs.FLAG_DRY_RUN | (infs.FLAG_KV_FP8 if fp8 else 0)))
+    for p in range(prompts):
+        ctx.prefill_shared(p, 0, 1024, None, None)
+    assert ctx.step_launch_plan([20 * s + 20 for s in range(64)], 64)[0]["cut"] == cut
     ctx.destroy()

@@ -1,8 +1,9 @@
 // Host check of the wavefront split of a step launch (plan_step_waves in
 // csrc/step_plan.h), built with g++ by tests/test_wave_plan.py: over random slot
 // lengths and launch shapes, the roles add up, there is a wavefront for every
-// item, every live response's pieces are whole page ranges that tile it, and
-// pieces stay within the limits per slot and per wavefront.  Chunk lengths are
+// item, every live response's pieces are whole page ranges that tile it,
+// pieces stay within the limits per slot and per wavefront, and no work-group
+// reads more than the split by work-groups would deal to one.  Chunk lengths are
 // drawn over the whole accepted range, the pieces a slot has room for as
 // infs_create sizes them: the chunks of the longest response, padded to whole
 // 128-byte lines of records.
@@ -38,10 +39,10 @@ int main() {
     StepRoles r{};
     if (!plan_step_waves(nj, S, uni(1, 4), npi, 256, len.data(), split, scmax, pieces.data(), &r)) continue;
     ++applied;
-    CHECK(S > kWaveMinSlots && r.cut);
+    CHECK(S > kWaveMinSlots && 2 * S > nj && r.cut);
     CHECK(r.n_merge >= 1 && r.n_suf >= 1 && r.n_pre >= (npi > 0) && r.n_pre <= npi);
     CHECK(r.n_pre + r.n_suf + r.n_merge == nj);
-    int items = 0;
+    int items = 0, largest = 0;
     for (int s = 0; s < S; ++s) {
       if (len[s] == 0) {
         CHECK(pieces[s] == 0);
@@ -55,9 +56,20 @@ int main() {
       for (int c = 0; c < n; ++c) {
         const int p = piece_first_page(c + 1, pages, n) - piece_first_page(c, pages, n);
         CHECK(p >= 1 && p <= kWavePagesMax);
+        largest = std::max(largest, p);
       }
     }
     CHECK(items == r.n_suffix_items && items <= r.n_suf * kWaves);
+    std::vector<int32_t> gp(S, 0);
+    const StepRoles g = plan_step_roles(nj, S, npi, 256, len.data(), split, scmax, gp.data());
+    std::vector<int> dealt(g.n_suf, 0);
+    for (int s = 0, it = 0; s < S; ++s)
+      for (int c = 0; c < gp[s]; ++c, ++it) {
+        const int pages = (len[s] + kPageTokens - 1) / kPageTokens;
+        const int pg = piece_first_page(c + 1, pages, gp[s]) - piece_first_page(c, pages, gp[s]);
+        dealt[it % g.n_suf] += g.cut ? pg * kPageTokens : std::min(split, len[s] - c * split);
+      }
+    CHECK(kWaves * largest * kPageTokens <= *std::max_element(dealt.begin(), dealt.end()));
   }
   std::printf("applied %d failures %d\n", applied, fails);
   return fails || applied < 1000;
