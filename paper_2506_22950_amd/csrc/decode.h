@@ -1664,7 +1664,7 @@ template <class SH>
 struct MergeWaveShape {
   static constexpr int OPP = SH::HPK * SH::D;
   static constexpr int MV = (OPP / 4 + 63) / 64;
-  static constexpr int MCW = MV == 1 ? 24 : MV == 2 ? 8 : 4;
+  static constexpr int MCW = merge_wave_partials(OPP);
 };
 
 template <class SH, bool L2, bool STEP>

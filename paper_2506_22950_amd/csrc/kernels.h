@@ -42,6 +42,9 @@ hipError_t launch_layers(const KernelKey& key, const StepArgs& args, int grid, h
 // resident at once (occupancy per compute unit times compute units).
 hipError_t layers_resident(const KernelKey& key, int* resident);
 
+// The same of the per-layer kernels.
+hipError_t decode_resident(const KernelKey& key, int* resident);
+
 // The decode kernel instantiations, spread over several translation units
 // (inst_*.hip) so that they compile in parallel.
 struct KernelEntry {

@@ -65,18 +65,25 @@ hipError_t launch_layers(const KernelKey& key, const StepArgs& args, int grid, h
   return hipGetLastError();
 }
 
-hipError_t layers_resident(const KernelKey& key, int* resident) {
-  const KernelEntry* e = find_entry(key);
-  if (!e) return hipErrorInvalidValue;
-  int per_cu = 0, waves_per_cu = 0, dev = 0, cus = 0;
-  hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, e->layers[0], kBlockThreads, 0);
-  if (err == hipSuccess)
-    err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&waves_per_cu, e->layers[2], kBlockThreads, 0);
+// Work-groups resident at once of whichever of two kernels fits fewer.
+static hipError_t resident_work_groups(void (*f)(const StepArgs), void (*g)(const StepArgs), int* resident) {
+  int f_per_cu = 0, g_per_cu = 0, dev = 0, cus = 0;
+  hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&f_per_cu, f, kBlockThreads, 0);
+  if (err == hipSuccess) err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&g_per_cu, g, kBlockThreads, 0);
   if (err == hipSuccess) err = hipGetDevice(&dev);
   if (err == hipSuccess) err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (err != hipSuccess) return err;
-  *resident = (per_cu < waves_per_cu ? per_cu : waves_per_cu) * cus;
-  return hipSuccess;
+  if (err == hipSuccess) *resident = (f_per_cu < g_per_cu ? f_per_cu : g_per_cu) * cus;
+  return err;
+}
+
+hipError_t layers_resident(const KernelKey& key, int* resident) {
+  const KernelEntry* e = find_entry(key);
+  return e ? resident_work_groups(e->layers[0], e->layers[2], resident) : hipErrorInvalidValue;
+}
+
+hipError_t decode_resident(const KernelKey& key, int* resident) {
+  const KernelEntry* e = find_entry(key);
+  return e ? resident_work_groups(e->decode[0], e->decode[2], resident) : hipErrorInvalidValue;
 }
 
 // Work-groups of a prefill over n units of work: one each, up to a grid the

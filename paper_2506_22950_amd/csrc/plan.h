@@ -26,6 +26,9 @@ constexpr int kRecordsPerLine = 16;   // (max, sum) records of 8 bytes per 128-b
 constexpr int kClockSlots = 16;        // timing slots per launch (see StepArgs::clock_start)
 constexpr int kClockStride = 16;       // uint64 per timing slot: one 128-byte line each
 constexpr int kMateWaitTicks = 2000;   // bound on a step-launch work-group's wait for its CU mate (100 MHz ticks)
+// Partials a merge wavefront loads at a time for `outputs` outputs (query rows of a
+// KV head times head size) of a slot, of which a lane holds four or more.
+constexpr int merge_wave_partials(int outputs) { return outputs <= 256 ? 24 : outputs <= 512 ? 8 : 4; }
 // Size of the file-scope device array that holds the split-K workspace and the
 // arrival counters of infs_decode_step_static (one copy per GPU, kept until the
 // process ends).

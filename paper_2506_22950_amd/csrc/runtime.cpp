@@ -69,6 +69,7 @@ struct infs_ctx {
   void* scratch = nullptr;  // this device's static scratch array (infs_decode_step_static)
   int layers_resident = 0;  // work-groups of the step-launch kernel resident at once (0: no step launch)
   int players_resident = 0; // the same for the probe kernel's step launch (0: none)
+  int decode_resident = 0, pdecode_resident = 0;  // work-groups of the per-layer kernels resident at once
   // host state
   std::vector<int32_t> plen;                       // per prompt, -1 before its first prefill
   std::vector<std::vector<uint8_t>> prefilled;     // [prompt][layer]
@@ -228,29 +229,21 @@ void reset_host(infs_ctx* c) {
   c->stats = infs_stats{};
 }
 
-// Work-groups of a per-layer launch.  Every one of them takes its place on the
-// GPU (two to a CU) for the length of the exchange, however little it reads: 64
-// probe samples of up to 16 tokens are 512 response and 512 merge work-groups in
-// three turns.  Where they do not fit at once and no response (bf16 Q/K/V) is
-// longer than a wavefront's share of a chunk, so that three wavefronts of a
-// response work-group had nothing to do, four responses, and four merges, share
-// a work-group, a wavefront each; the partials are the same.  Prefill and 16 probe
-// steps of 64 samples, 28 layers, prompt 2048: 8608 us before, 7606 with it.
-// Longer responses would be cut otherwise than in a step launch of split mode 0,
-// and take more than one load round.
-constexpr int kResidentWorkGroups = 512;  // 256 CUs
-constexpr int kShortResponse = 64;
-int per_layer_grid(const infs_ctx* c, const infs::KernelKey& key, StepArgs& a) {
+// Work-groups of a per-layer launch of the kernel `key`, of which `resident` fit
+// the GPU at once (see short_responses_pay).
+int per_layer_grid(const infs_ctx* c, const infs::KernelKey& key, int resident, StepArgs& a) {
   const int lives = a.n_merge_items;
-  int grid = (a.n_prefix_items + a.n_suffix_items + a.n_zero_items + lives) * c->Hkv;
-  a.resp_cut = 0;
-  int longest = 0;
+  int longest = 0, chunks = 0;
   for (int s = 0; s < a.S; ++s) longest = std::max(longest, a.slot[s].len);
-  if (key.bf16 && grid > kResidentWorkGroups && longest <= std::min(kShortResponse, c->split / infs::kWaves)) {
+  for (int p = 0; p < a.num_prompts; ++p) chunks = std::max(chunks, a.prompt[p].nchunks);
+  const int busy = (a.n_prefix_items + a.n_suffix_items + lives) * c->Hkv;
+  a.resp_cut = 0;
+  if (key.bf16 && resident > 0 && longest <= std::min(infs::kShortResponse, c->split / infs::kWaves) &&
+      infs::short_responses_pay(busy, resident, chunks + 1, key.hpk * key.head_dim)) {
     a.resp_cut = 2;
-    grid = (a.n_prefix_items + a.n_zero_items + 2 * ceil_div(lives, infs::kWaves)) * c->Hkv;
+    return (a.n_prefix_items + a.n_zero_items + 2 * ceil_div(lives, infs::kWaves)) * c->Hkv;
   }
-  return grid;
+  return busy + a.n_zero_items * c->Hkv;
 }
 
 // Build the plan of the step that is about to open: lengths after the append,
@@ -324,7 +317,7 @@ infs_status open_step(infs_ctx* c) {
   a.live_mask = 0;
   for (int s = 0; s < c->S; ++s)
     if (a.slot[s].len > 0) a.live_mask |= uint64_t(1) << s;
-  c->grid = per_layer_grid(c, c->key, a);
+  c->grid = per_layer_grid(c, c->key, c->decode_resident, a);
   c->step_bytes = bytes;
   c->step_flops = flops;
   c->step_open = true;
@@ -404,7 +397,7 @@ infs_status open_probe(infs_ctx* c, int p, int first, int n, const uint8_t* live
   a.live_mask = 0;
   for (int j = 0; j < n; ++j)
     if (a.slot[j].len > 0) a.live_mask |= uint64_t(1) << j;
-  c->pgrid = per_layer_grid(c, c->pkey, a);
+  c->pgrid = per_layer_grid(c, c->pkey, c->pdecode_resident, a);
   c->pstep_bytes = bytes;
   c->pstep_flops = flops;
   c->pb_prompt = p;
@@ -699,18 +692,20 @@ infs_status infs_create(const infs_config* cfg, void* hip_stream, infs_ctx** out
       if (e != hipSuccess) return fail(nullptr, INFS_E_DEVICE, "hipMemset(%s): %s", what, hipGetErrorString(e));
       return INFS_OK;
     };
-    const hipError_t oe = infs::layers_resident(key, &c->layers_resident);
+    hipError_t oe = infs::layers_resident(key, &c->layers_resident);
+    if (oe == hipSuccess) oe = infs::decode_resident(key, &c->decode_resident);
     if (oe != hipSuccess) {
       delete c;
-      return device_fail(nullptr, oe, "occupancy query of the step launch");
+      return device_fail(nullptr, oe, "occupancy query of the decode kernels");
     }
     // a step launch needs at least one producer and one merge work-group per KV head
     if (c->layers_resident / c->Hkv < 2) c->layers_resident = 0;
     if (c->probe_k > 0) {
-      const hipError_t pe = infs::layers_resident(c->pkey, &c->players_resident);
+      hipError_t pe = infs::layers_resident(c->pkey, &c->players_resident);
+      if (pe == hipSuccess) pe = infs::decode_resident(c->pkey, &c->pdecode_resident);
       if (pe != hipSuccess) {
         delete c;
-        return device_fail(nullptr, pe, "occupancy query of the probe step launch");
+        return device_fail(nullptr, pe, "occupancy query of the probe kernels");
       }
       if (c->players_resident / c->Hkv < 2) c->players_resident = 0;
     }

@@ -286,4 +286,32 @@ inline bool plan_step_waves(int nj, int S, int prompts, int n_prefix_items, int 
   return true;
 }
 
+// Whether a per-layer launch of bf16 Q/K/V whose responses are all at most
+// kShortResponse tokens (a load round of a wavefront) and at most its share of a
+// chunk gives each response and each merge a wavefront, four to a work-group.
+// Every work-group takes its place on the GPU for the length of the exchange,
+// however little it reads: 64 probe samples of up to 16 tokens are 512 response and
+// 512 merge work-groups, in three turns with the prefix chunks.  `busy` counts the
+// prefix, response and merge work-groups; the ones that clear idle slots leave at
+// once.  `partials` is the most a slot merges: a merge work-group loads them with
+// four wavefronts, a merge wavefront alone, so it pays
+// * past one turn where a merge is one round of loads.  12 per-layer launches of
+//   responses up to 40 tokens, us without and with it, 16/8 heads of 128: prompt
+//   2048, 1152 work-groups 229 and 186, 640 186 and 177, 512 177 and 178; prompt 256,
+//   528 161 and 152, 400 144 and 151; E4M3, 1088 199 and 193, 448 172 and 181; 4 KV
+//   heads 544 170 and 159; 8/8 heads 1088 198 and 157, but 960 153 and 156.  The length
+//   matters little: prompt 2048, 1152 work-groups, up to 64 tokens 232 and 190, up to
+//   17 tokens 222 and 185.
+// * past two turns with two or three rounds.  32/8 heads of 128, prompts up to 1500,
+//   1248 work-groups 248 and 205, 992 236 and 198, 736 168 and 190; up to 2000, 1280
+//   260 and 228, 768 184 and 213; head size 64, 64/8 heads, 1192 216 and 174, 808 152
+//   and 155; 4 KV heads, prompt 4000, 640 195 and 203.
+// * not with more: 32/8 heads, prompts up to 4096, 1488 work-groups 332 and 373.
+// Longer responses would be cut otherwise than in a step launch of split mode 0.
+constexpr int kShortResponse = 64;
+inline bool short_responses_pay(int busy, int resident, int partials, int outputs) {
+  const int rounds = step_plan_detail::cdiv(partials, merge_wave_partials(outputs));
+  return rounds <= 1 ? busy > resident : rounds <= 3 && busy > 2 * resident;
+}
+
 }  // namespace infs

@@ -1,5 +1,5 @@
 // Host check of the wavefront split of a step launch (plan_step_waves in
-// csrc/step_plan.h), built with g++ by tests/test_wave_plan.py: over random slot
+// csrc/step_plan.h) and of the line for short responses in per-layer launches, built with g++ by tests/test_wave_plan.py: over random slot
 // lengths and launch shapes, the roles add up, there is a wavefront for every
 // item, every live response's pieces are whole page ranges that tile it,
 // pieces stay within the limits per slot and per wavefront, and no work-group
@@ -71,6 +71,15 @@ int main() {
       }
     CHECK(kWaves * largest * kPageTokens <= *std::max_element(dealt.begin(), dealt.end()));
   }
+  // short responses a wavefront each (512 resident work-groups), measured shapes on both sides of the
+  // line: busy work-groups, partials of a merge, outputs of a merge, and whether it was faster
+  const struct { int busy, partials, outputs; bool pays; } shorts[] = {
+      {1152, 17, 256, true}, {640, 17, 256, true}, {512, 17, 256, false}, {384, 17, 256, false}, {400, 3, 256, false},
+      {448, 9, 256, false}, {640, 33, 256, false}, {1248, 13, 512, true}, {736, 13, 512, false}, {576, 9, 512, false},
+      {616, 13, 512, false}, {768, 17, 512, false}, {1488, 33, 512, false}, {976, 33, 512, false}, {640, 9, 1024, false},
+      {560, 4, 1024, true}, {2560, 9, 1024, true}, {2208, 5, 512, true}};
+  for (int cs = 0; cs < (int)(sizeof shorts / sizeof *shorts); ++cs)
+    CHECK(short_responses_pay(shorts[cs].busy, 512, shorts[cs].partials, shorts[cs].outputs) == shorts[cs].pays);
   std::printf("applied %d failures %d\n", applied, fails);
   return fails || applied < 1000;
 }
