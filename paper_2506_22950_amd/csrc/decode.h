@@ -15,6 +15,8 @@
 //   * log-sum-exp merge: one work-group per live (slot, KV head), placed at
 //     the end of the grid, waits (bounded) until every chunk of that slot has
 //     published its partial, combines the partial softmaxes and writes O.
+// Short responses and their merges take a wavefront each, four to a work-group,
+// where the launch would not fit the GPU at once (StepArgs::resp_cut).
 // Idle slots get O = 0.
 //
 // A partial over a key set J is (M, L, O) with scores in log2 units
@@ -515,7 +517,6 @@ struct RespMfma {
     KUnit k[NPG][KB];
     VPair v[NPG / 2][DB];
   };
-  static constexpr int kLoads = NPG * (KB + DB);  // load instructions of one round
   // Running partial: O^T tiles, m per column and, in lt, the column's sum of
   // probabilities (every element; an all-ones V^T tile through the same MFMA).
   struct Acc {
@@ -777,7 +778,6 @@ struct RowTile {
     u32x4 k[NG][MBS][KB];
     VReg v[NG][MBS][4][NV];
   };
-  static constexpr int kLoads = NG * MBS * (KB + 4 * NV);
   struct Acc {
     f32x4 o[NT];
     float m, l;  // l: this lane's share of the row's sum
@@ -1611,34 +1611,6 @@ __device__ __forceinline__ bool reached(const int32_t* ctr, int32_t target) {
   return (int32_t)((uint32_t)v - (uint32_t)target) >= 0;
 }
 
-// Merge block of (slot s, KV head g): wait until the prefix chunks of its
-// prompt and its own response chunks have all arrived on its counter
-// (bounded), then merge.
-template <class SH, bool L2>
-__device__ void merge_block(const StepArgs& a, int s, int g, unsigned long long* flag, float* smem) {
-  if (threadIdx.x == 0) {
-    const int32_t* sc = slot_counter(a, s, g);
-    const int32_t target = a.slot[s].target;
-    bool ok = false;
-    if (a.merge_polls >= 0) {
-      ok = reached(sc, target);
-      for (int spins = 0; !ok && spins < a.merge_polls; ++spins) {
-        __builtin_amdgcn_s_sleep(2);
-        ok = reached(sc, target);
-      }
-    }
-    *flag = ok;
-  }
-  __syncthreads();
-  if (!*flag) {
-    if (threadIdx.x == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    float* o = a.o + ((int64_t)s * a.Hq + g * SH::HPK) * SH::D;
-    for (int idx = threadIdx.x; idx < SH::HPK * SH::D; idx += kBlockThreads) o[idx] = __builtin_nanf("");
-    return;
-  }
-  merge_outputs<SH, L2>(a, s, g, smem);
-}
-
 // One lane: wait until *ctr has reached target, polling at most merge_polls
 // times.  Gives up at once when merge_polls < 0 or, in a step launch,
 // when the status word shows that another wait has given up.
@@ -1653,6 +1625,21 @@ __device__ bool bounded_wait(const StepArgs& a, const int32_t* ctr, int32_t targ
   return false;
 }
 
+// Merge block of (slot s, KV head g): wait until the prefix chunks of its
+// prompt and its own response chunks have all arrived on its counter
+// (bounded), then merge.
+template <class SH, bool L2>
+__device__ void merge_block(const StepArgs& a, int s, int g, unsigned long long* flag, float* smem) {
+  if (threadIdx.x == 0) *flag = bounded_wait(a, slot_counter(a, s, g), a.slot[s].target, false);
+  __syncthreads();
+  if (!*flag) {
+    if (threadIdx.x == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    float* o = a.o + ((int64_t)s * a.Hq + g * SH::HPK) * SH::D;
+    for (int idx = threadIdx.x; idx < SH::HPK * SH::D; idx += kBlockThreads) o[idx] = __builtin_nanf("");
+    return;
+  }
+  merge_outputs<SH, L2>(a, s, g, smem);
+}
 
 // One wavefront merges every partial of (slot s, KV head g) of a layer and
 // writes O rows g*hpk .. +hpk-1 (the log-sum-exp combination of the split-K

@@ -111,15 +111,12 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// A producer work-group has stored its partial and then issued the loads of its
-// next item (NEXT load instructions per wavefront, 0 without a next item): once
-// every wavefront's stores have completed -- all but its NEXT most recent
-// memory operations -- count one arrival on each live slot among first ..
-// first + n - 1, as arrive() does.  The next item's loads stay in flight.
-template <int NEXT>
+// A producer work-group has stored its partial: once every wavefront's stores
+// have completed, count one arrival on each live slot among first ..
+// first + n - 1, as arrive() does.
 __device__ __forceinline__ void arrive_behind(const StepArgs& a, int first, int n, int g) {
   asm volatile("" ::: "memory");
-  wait_vmcnt<NEXT>();
+  wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   // liveness from the plan's bitmask: reading a.slot[first + lane] would be a
@@ -276,7 +273,6 @@ struct PrefixMfma {
   struct Regs {
     bf16x8 ka[2][KB], va[DB], kn[2][KB], vn[DB];
   };
-  static constexpr int kBlockLoads = 2 * KB + DB;  // load instructions of one block
   // This wavefront's blocks [b0, b1) of the chunk: its token group's share of
   // the chunk's blocks (a step launch's chunks hold twice the per-layer
   // launch's, see kStepPrefixSplit).
@@ -305,15 +301,9 @@ struct PrefixMfma {
 #pragma unroll
     for (int db = 0; db < DB; ++db) va[db] = __builtin_bit_cast(bf16x8, ld_kv<SH, false>(vblk + (db * 64 + lane) * 8 * SH::KES));
   }
-  // Whether issue() also loads the wavefront's second block.
-  __device__ __forceinline__ static bool pre_next(const PrefixItem& it) {
-    int nblk, b0, b1;
-    blocks(it, nblk, b0, b1);
-    return ISSUE_TWO && b0 + 1 < b1;
-  }
   // The wavefront's first block (a wavefront without blocks loads the chunk's
   // last block -- in bounds, never used) and, with one tile per wavefront, its
-  // second: kBlockLoads or 2 * kBlockLoads load instructions.
+  // second.
   __device__ __forceinline__ static void issue(const StepArgs& a, const LayerView& V, const PrefixItem& it, int g, Regs& R) {
     int nblk, b0, b1;
     blocks(it, nblk, b0, b1);
@@ -517,7 +507,6 @@ template <class SH, bool L2>
 struct Resp {
   static constexpr int HPK = SH::HPK;
   using Regs = WaveRegs<SH, HPK>;
-  static constexpr int kLoads = 2 * Regs::U;
   __device__ __forceinline__ static void issue(const StepArgs& a, const LayerView& V, const RespItem& r, int pages, int g, Regs& R) {
     SuffixAddr<SH> ad{(const char*)V.pool, pages, a.Hkv, g};
     wave_load_round<SH, HPK>(ad, r.wt0, r.has_new ? r.last : r.wt1, r.wt0, R);
@@ -568,7 +557,6 @@ struct RespTiles {
   using RM = RespMfma<SH>;
   using Regs = typename RM::Regs;
   static constexpr int HPK = SH::HPK;
-  static constexpr int kLoads = RM::kLoads;
   __device__ __forceinline__ static void issue(const StepArgs& a, const LayerView& V, const RespItem& r, int pages, int g, Regs& R) {
     RM::load_round(V.pool, pages, a.Hkv, g, 0, R);
   }
@@ -741,7 +729,7 @@ __device__ __forceinline__ void prefix_loop(const StepArgs& a, int g, int jp, fl
       const PrefixItem it = prefix_item(a, jp + k * a.n_pre_wg);
       P::finish(a, V, it, g, smem, R, [&]() { layer_gate(a, it.p, l, ready); },
                 [&]() {
-                  arrive_behind<0>(a, it.p * a.m, a.m, g);
+                  arrive_behind(a, it.p * a.m, a.m, g);
                   if (k + 1 < nk) {
                     P::issue(a, V, prefix_item(a, jp + (k + 1) * a.n_pre_wg), g, R);
                   } else {
@@ -777,7 +765,7 @@ __device__ __forceinline__ void suffix_loop(const StepArgs& a, int g, int jr, fl
       P::finish(a, V, it, pages, g, smem, R, [&]() { layer_gate(a, it.s / a.m, l, ready); },
                 [&]() {
                   if (!has_next) {
-                    arrive_behind<0>(a, it.s, 1, g);
+                    arrive_behind(a, it.s, 1, g);
                     if (threadIdx.x == 0) peer_mark(a, l, 0);
                     return;
                   }
@@ -786,7 +774,7 @@ __device__ __forceinline__ void suffix_loop(const StepArgs& a, int g, int jr, fl
                   // waits for this item's stores.
                   const RespItem nx = resp_item(a, jr + (k + 1 < nk ? k + 1 : 0) * a.n_suf_wg);
                   if (nk != 1) pages = resp_pages(a, nx);
-                  arrive_behind<0>(a, it.s, 1, g);
+                  arrive_behind(a, it.s, 1, g);
                   if (ln != l) {  // the next item is in the next layer: let the CU mate finish this one first
                     if (threadIdx.x == 0) peer_mark(a, l, 0);
                     mate_gate(a, l);
