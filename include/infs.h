@@ -341,9 +341,9 @@ infs_status infs_set_exchange(infs_ctx* ctx, int32_t mode);
    Where the per-layer prefix chunks would give some work-group two items, mode 1 also takes the
    prefix in chunks of 256 tokens on MFMA tiles, bf16 or E4M3 cache (two per-layer chunks, walked by
    the same work-group), which leaves more work-groups for the responses.
-   With more than 32 slots, more than half as many as work-groups per KV head, mode 1 gives every
-   wavefront of a response work-group a response piece of its own instead, with fewer merge work-groups,
-   where a work-group then reads no more of a layer (bf16 Q/K/V; E4M3 caches up to 64 prefix rows;
+   With more than 32 slots, more than half as many as work-groups per KV head, of which 12 are live,
+   mode 1 gives every wavefront of a response work-group a response piece of its own instead, with fewer
+   merge work-groups, where a work-group then reads no more of a layer (bf16 Q/K/V;
    infs_step_launch_plan tells which split a step gets).
    mode 0: responses in chunks of split_tokens, the prefix in the per-layer launch's chunks, and
            work-groups divided in proportion to the chunk counts, the partition of infs_decode_step:

@@ -127,7 +127,7 @@ __device__ __forceinline__ void arrive_behind(const StepArgs& a, int first, int 
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Wavefront path registers: one load round of K and V (U 16-byte chunks each).
+// Registers of the wavefront dot products: one load round of K and V (U 16-byte chunks each).
 template <class SH, int NR>
 struct WaveRegs {
   static constexpr int U = WaveCfg<SH, NR>::U;

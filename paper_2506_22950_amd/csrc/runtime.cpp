@@ -870,8 +870,8 @@ int plan_split(const infs_ctx* c, const KernelKey& key, int nj, int S, int promp
     *roles = infs::plan_step_roles_chunks(nj, S, n_prefix_items, lens, c->split, pieces);
     return 0;
   }
-  const bool waves = key.bf16 && !(key.kv8 && key.prefix_rows > 64);  // see plan_step_waves
-  if (waves && infs::plan_step_waves(nj, S, prompts, n_prefix_items, prefix_split, lens, c->split, c->scmax, pieces, roles))
+  if (key.bf16 && infs::plan_step_waves(nj, S, prompts, n_prefix_items, prefix_split, lens, c->split, c->scmax, pieces, roles,
+                                        key.kv8 && key.prefix_rows > 64))
     return 2;
   *roles = infs::plan_step_roles(nj, S, n_prefix_items, prefix_split, lens, c->split, c->scmax, pieces);
   return roles->cut ? 1 : 0;

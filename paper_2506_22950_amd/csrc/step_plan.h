@@ -183,7 +183,7 @@ inline StepRoles plan_step_roles(int nj, int S, int n_prefix_items, int prefix_s
   return r;
 }
 
-// Most tokens the plan deals to one response work-group of a KV head (0 < n_suf <
+// Most tokens, in whole pages, the plan deals to one response work-group of a KV head (0 < n_suf <
 // 2 * kMaxSlots of them; work-group i takes items i, i + n_suf, ... of the slots'
 // pieces in order).
 inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, int split, const int32_t* pieces) {
@@ -193,8 +193,9 @@ inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, i
     const int pages = step_plan_detail::cdiv(len[s], kPageTokens);
     for (int c = 0; c < pieces[s]; ++c, ++it) {
       int32_t& t = tokens[it % r.n_suf];
-      t += r.cut ? (piece_first_page(c + 1, pages, pieces[s]) - piece_first_page(c, pages, pieces[s])) * kPageTokens
-                 : len[s] - c * split < split ? len[s] - c * split : split;
+      const int first = r.cut ? piece_first_page(c, pages, pieces[s]) : c * (split / kPageTokens);
+      const int next = r.cut ? piece_first_page(c + 1, pages, pieces[s]) : first + split / kPageTokens;
+      t += ((next < pages ? next : pages) - first) * kPageTokens;
       if (t > most) most = t;
     }
   }
@@ -209,7 +210,7 @@ inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, i
 // here every wavefront has one.  The price is more partials, which the merges
 // pay.  It is taken where all of these hold (us a step of 12 layers, without and
 // with it, 32/8 heads of 128 on four prompts of 256 to 4096 tokens or 16/8 heads
-// on one of 1024, unless said otherwise):
+// on one of 1024, unless said otherwise; ms are whole group decodes):
 // * Four times its largest piece, what a work-group then reads, is no more than
 //   plan_step_roles deals to a work-group.  Four prompts, 64 slots up to 256
 //   tokens 404 and 288, up to 700 tokens 499 and 404, up to 2048 tokens 934 and
@@ -221,7 +222,12 @@ inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, i
 // * kWaveMinItems4 / 4 per-layer chunks to a response work-group and more: one
 //   prompt, 64 slots up to 300 tokens (1.6) 298 and 308, 48 live (1.2) 274 and
 //   301; at the line 48 live up to 700 tokens 295 and 305, but four prompts,
-//   64 slots up to 256 tokens (1.9) the 404 and 288 above.
+//   64 slots up to 256 tokens (1.9) the 404 and 288 above.  kWaveMinCut4 / 4 where
+//   plan_step_roles cuts, so every work-group has one piece: the steps of a decode
+//   on 40 slots (prompt 2048, 1.8 to 2.1) 627 ms and 701.
+// * kWaveMinLive live slots: fewer are cut into up to 32 partials each.  64 slots on
+//   four prompts, 36 layers, the steps with 4 to 11 live 3496 ms and 4013, with 20 to
+//   31 live 2180 and 2068; head size 64 (12 layers) 642 and 649, with 20 to 39 520 and 440.
 // * More than kWaveMinSlots slots, and more than half as many as work-groups per
 //   KV head.  The merge work-groups it frees are few with fewer: 32 slots up to
 //   2048 tokens (28 layers) 860 and 923, 16 slots 472 and 621.  With 4 KV heads
@@ -229,11 +235,17 @@ inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, i
 //   to 4000 tokens on two prompts 680 and 812, on one 663 and 594, up to 6000
 //   tokens 996 and 947, 48 live 716 and 752; 2 KV heads up to 9000 tokens (6
 //   layers) 334 and 371.
-// * Not E4M3 pages under a 128-row prefix tile (the caller's check): one prompt of
-//   2048, 64 slots up to 500 tokens 314 and 323, up to 1000 tokens 371 and 530, up
-//   to 2000 tokens 560 and 605.  Under 64 rows and fewer: four prompts, up to 256
-//   tokens 346 and 264, up to 2048 tokens 617 and 596, 16 rows up to 1500 tokens
-//   473 and 295.
+// * For E4M3 pages under a 128-row prefix tile (`wide_e4m3`) not in place of whole
+//   chunks dealt round robin: one prompt of 2048, 64 slots up to 500 tokens 314 and
+//   323, up to 1000 tokens 371 and 530, up to 2000 tokens 560 and 605; in place of cut
+//   pieces, the steps of a decode on 64 slots with 12 to 31 live 662 ms and 560.  Under
+//   64 rows and fewer in place of both: four prompts, up to 256 tokens 346 and 264, up
+//   to 2048 tokens 617 and 596, 16 rows up to 1500 tokens 473 and 295.
+// Whole group decodes without it, and with it by this rule: 64 slots on four prompts
+// (36 layers) 13936 ms and 12705, its E4M3 cache (12 layers) 3770 and 3635, d = 64 2940
+// and 2235; one prompt, 64 slots 2125 and 1973; two prompts of 32 slots 2015 and 1758;
+// three of 16 2257 and 1924; eight of 8 2993 and 2445; 16 KV heads (8 layers) 5911 and
+// 5241.
 //
 // A merge work-group only waits while the others load, so the merges run on
 // fewer than one wavefront each: two to a wavefront, and four where more than two
@@ -247,13 +259,20 @@ inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, i
 // The prefix is weighed kWavePrefixCost halves, as its chunks are walked after
 // the layer's queries arrive.
 // False where it does not apply, or where pieces would not fit a wavefront.
-constexpr int kWaveMinSlots = 32, kWaveMinItems4 = 7, kWaveDeepItems = 5, kWavePrefixCost = 3;
+constexpr int kWaveMinSlots = 32, kWaveMinLive = 12, kWaveMinItems4 = 7, kWaveMinCut4 = 9;
+constexpr int kWaveDeepItems = 5, kWavePrefixCost = 3;
 constexpr int kWavePagesMax = 64;  // a wavefront holds the page numbers of its piece one per lane
 inline bool plan_step_waves(int nj, int S, int prompts, int n_prefix_items, int prefix_split, const int32_t* len, int split, int scmax,
-                            int32_t* pieces, StepRoles* out) {
+                            int32_t* pieces, StepRoles* out, bool wide_e4m3 = false) {
   using namespace step_plan_detail;
   StepRoles r = plan_step_roles_chunks(nj, S, n_prefix_items, len, split, pieces);
   if (S <= kWaveMinSlots || 2 * S <= nj || 4 * r.n_suffix_items < kWaveMinItems4 * r.n_suf) return false;
+  int live = 0;
+  for (int s = 0; s < S; ++s) live += len[s] > 0;
+  if (live < kWaveMinLive) return false;
+  const StepRoles groups = plan_step_roles(nj, S, n_prefix_items, prefix_split, len, split, scmax, pieces);
+  if (groups.cut ? 4 * r.n_suffix_items < kWaveMinCut4 * r.n_suf : wide_e4m3) return false;
+  const int dealt = groups.n_suf > 0 ? most_response_tokens(groups, S, len, split, pieces) : 0;
   const int merges = prompts > 2 && r.n_suffix_items < kWaveDeepItems * r.n_suf ? 4 : 2;  // to a wavefront
   r.n_merge = cdiv(S, merges * kWaves) < nj - 1 ? cdiv(S, merges * kWaves) : nj - 1;
   const int prod = nj - r.n_merge;
@@ -276,8 +295,6 @@ inline bool plan_step_waves(int nj, int S, int prompts, int n_prefix_items, int 
   if (best < 0) return false;
   r.n_pre = best_pre;
   r.n_suf = prod - best_pre;
-  const StepRoles groups = plan_step_roles(nj, S, n_prefix_items, prefix_split, len, split, scmax, pieces);
-  const int dealt = groups.n_suf > 0 ? most_response_tokens(groups, S, len, split, pieces) : 0;
   if (cut_responses(len, S, r.n_suf * kWaves, scmax, pieces, kWavePagesMax) * kPageTokens * kWaves > dealt) return false;
   r.cut = true;
   r.n_suffix_items = 0;

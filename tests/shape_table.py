@@ -3,7 +3,7 @@ workload that selects it.
 
 Selection (infs_create): the prefix runs on MFMA tiles iff the type is bf16 and
 a prompt has at least 16 query rows per KV head (m * hpk); the row tile is the
-smallest of 8/16 (wavefront path) or 16/32/64/128 (MFMA) that holds them.  The
+smallest of 8/16 (plain rows) or 16/32/64/128 (MFMA) that holds them.  The
 probe launches of prefix reuse use the decode kernel's path with
 probe_batch * hpk rows.  A bf16 wavefront tile of 16 rows with 8 query heads
 per KV head is reached only that way (m = 1 decodes 8 rows, a probe batch of 2

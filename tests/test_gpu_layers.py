@@ -62,7 +62,7 @@ def test_step_launch_bf16_mfma32_four_layers():
 
 
 def test_step_launch_f32_wave_every_step():
-    # fp32 wavefront path, three layers, three prefix chunks, responses to 400.
+    # fp32 plain rows, three layers, three prefix chunks, responses to 400.
     cfg = get_config("tiny_f32").with_(layers=3, prompt_lens=(300,), length_dist=("uniform", 1, 400),
                                        max_suffix_len=400)
     _layers_case(cfg, "fifo", every=1)
@@ -78,7 +78,7 @@ def test_step_launch_hpk4_three_prompts():
 
 
 def test_step_launch_bf16_wave_single_slot():
-    # m=1: 2 prefix rows on the bf16 wavefront path.
+    # m=1: 2 prefix rows on the bf16 row tile.
     cfg = get_config("qwen3_1p7b_l1_g32").with_(layers=3, slots_per_prompt=1, samples_per_prompt=4,
                                                 prompt_lens=(257,), length_dist=("lognormal", 4.0, 0.8, 1, 300),
                                                 max_suffix_len=300)
@@ -260,7 +260,7 @@ def test_probe_step_launch_hpk4_two_prompts():
 
 
 def test_probe_step_launch_f32_wave():
-    # fp32 wavefront path: batches of 8 samples (16 rows), three layers.
+    # fp32 plain rows: batches of 8 samples (16 rows), three layers.
     _probe_case(get_config("tiny_f32").with_(layers=3), "fifo", 5, split=0)
 
 
@@ -290,7 +290,7 @@ def _count_cut_steps(cfg, log, nj, split, mfma):
 def test_step_launch_cut_pieces_multi_round(name):
     # Long responses on few slots: the per-layer chunks outnumber the response work-groups, so
     # the step launch cuts the responses into pieces of several load rounds per wavefront
-    # (MFMA tiles on bf16 and E4M3 pages, and the fp32 wavefront path); checked against the
+    # (MFMA tiles on bf16 and E4M3 pages, and the fp32 plain rows); checked against the
     # oracle, and the test asserts that the cut path ran.
     kv_fp8 = name == "e4m3_mfma"
     if name in ("bf16_mfma", "e4m3_mfma"):

@@ -38,7 +38,7 @@ def test_tiny_f32_every_step(policy):
 
 
 def test_tiny_f32_multichunk_ragged():
-    # fp32 wavefront path over several split-K chunks with ragged tails:
+    # fp32 plain rows over several split-K chunks with ragged tails:
     # P=300 with 128-token chunks, responses up to 400.
     cfg = get_config("tiny_f32").with_(prompt_lens=(300,), length_dist=("uniform", 1, 400), max_suffix_len=400)
     _run_and_check(cfg, "fifo", split=128, capture=lambda log: sample_steps(log, every=3))
@@ -71,7 +71,7 @@ def test_bf16_long_split_chunks(split):
 
 
 def test_f32_wave_split_1024():
-    # fp32 wavefront path with 1024-token response chunks: responses up to 2500.
+    # fp32 plain rows with 1024-token response chunks: responses up to 2500.
     cfg = get_config("tiny_f32").with_(prompt_lens=(200,), length_dist=("uniform", 1, 2500), max_suffix_len=2500)
     _run_and_check(cfg, "fifo", split=1024, capture=lambda log: sample_steps(log, every=40, refills=8))
 
@@ -152,12 +152,12 @@ def test_bf16_prefix_reuse_hpk4():
 
 
 def test_f32_prefix_reuse_wave():
-    # fp32 wavefront path: probe batches of 8 samples (16 rows).
+    # fp32 plain rows: probe batches of 8 samples (16 rows).
     _prefix_reuse(get_config("tiny_f32"), "fifo", 5, split=0)
 
 
 def test_bf16_single_slot_wave_prefix():
-    # m=1: 2 prefix rows, so the prefix runs on the wavefront path in bf16.
+    # m=1: 2 prefix rows, so the prefix runs on the row tile in bf16.
     cfg = get_config("qwen3_1p7b_l1_g32").with_(slots_per_prompt=1, samples_per_prompt=4, prompt_lens=(257,),
                                                 length_dist=("lognormal", 4.0, 0.8, 1, 300), max_suffix_len=300)
     _run_and_check(cfg, "fifo", capture=lambda log: sample_steps(log, every=5))
@@ -235,7 +235,7 @@ def test_bf16_scale_and_wide_scores(case):
                                                     length_dist=("lognormal", 4.0, 1.0, 1, 260),
                                                     max_suffix_len=260, pool_rows=None, qk_scale=wide)
         scale = 0.0
-    else:                              # m=1: 2 prefix rows, the bf16 wavefront path
+    else:                              # m=1: 2 prefix rows, the bf16 row tile
         cfg = get_config("qwen3_1p7b_l1_g32").with_(slots_per_prompt=1, samples_per_prompt=4, prompt_lens=(600,),
                                                     length_dist=("lognormal", 4.0, 0.8, 1, 300), max_suffix_len=300,
                                                     qk_scale=wide if case == "wave_bf16_wide" else None)
@@ -246,7 +246,7 @@ def test_bf16_scale_and_wide_scores(case):
 
 @pytest.mark.parametrize("case", ["scale_half", "wide"])
 def test_f32_scale_and_wide_scores(case):
-    # fp32 wavefront path at 1e-5, d=64, three prefix chunks of 128 tokens:
+    # fp32 plain rows at 1e-5, d=64, three prefix chunks of 128 tokens:
     # scale 0.5 (four times the default), or Q x 4 with K rows ramped 0.1 -> 2.
     cfg = get_config("tiny_f32").with_(prompt_lens=(300,), length_dist=("uniform", 1, 400), max_suffix_len=400)
     if case == "wide":

@@ -67,7 +67,7 @@ int main() {
       for (int c = 0; c < gp[s]; ++c, ++it) {
         const int pages = (len[s] + kPageTokens - 1) / kPageTokens;
         const int pg = piece_first_page(c + 1, pages, gp[s]) - piece_first_page(c, pages, gp[s]);
-        dealt[it % g.n_suf] += g.cut ? pg * kPageTokens : std::min(split, len[s] - c * split);
+        dealt[it % g.n_suf] += kPageTokens * (g.cut ? pg : std::min(split / kPageTokens, pages - c * split / kPageTokens));
       }
     CHECK(kWaves * largest * kPageTokens <= *std::max_element(dealt.begin(), dealt.end()));
   }
