@@ -43,11 +43,12 @@
 // only once its CU mate is past its part of the layer (or after a short
 // bound), and the host places the merge work-groups on the CUs of prefix
 // work-groups, which load little.  A prefix work-group, whose partial is needed
-// early, loads its next layer's chunk as soon as its partial is counted: the
-// chunk is there when the layer may start (12 layers of short responses, d = 64:
-// 106.7 us a step against 115.3 with the loads issued at the layer's start; the
-// first step of a 2048-token prompt, 28 layers: 268 against 280; long responses
-// the same).  Which work-groups share a CU is read from the hardware (see
+// early, loads its next layer's chunk as soon as its partial is counted, so that
+// the chunk is there when the layer may start, or only then where those loads
+// would hold up the layer's merges (early_prefix_pays): 12 layers of short
+// responses, d = 64, 106.7 us a step against 115.3 with the loads at the layer's
+// start; the first step of a 2048-token prompt, 28 layers, 268 against 280.
+// Which work-groups share a CU is read from the hardware (see
 // mate_gate); none of this affects results.
 #pragma once
 #include <type_traits>
@@ -713,20 +714,27 @@ __device__ __forceinline__ void layer_gate(const StepArgs& a, int p, int l, uint
 }
 
 // Prefix-chunk work-group jp of KV head g: prefix items jp, jp + n_pre_wg, ...
-// of every layer, each loaded right behind the previous item's arrival, also
-// across layers.
+// of every layer, each loaded right behind the previous item's arrival, with
+// StepArgs::prefix_early also across layers.
 template <class SH, bool L2>
 __device__ __forceinline__ void prefix_loop(const StepArgs& a, int g, int jp, float* smem) {
   if (jp >= a.n_prefix_items) return;
   const int nk = (a.n_prefix_items - jp + a.n_pre_wg - 1) / a.n_pre_wg;
   using P = std::conditional_t<SH::MFMA, PrefixMfma<SH, L2>, PrefixTile<SH, L2>>;
   typename P::Regs R;
-  P::issue(a, layer_view(a, 0), prefix_item(a, jp), g, R);
+  // a choice of the shapes that have one only: elsewhere the second place costs registers (d = 64, 15
+  // slots, 12 layers, 107.5 us against 106.1)
+  const bool early = !early_prefix_varies(SH::MFMA, SH::KV8, SH::D, SH::PR) || a.prefix_early;
+  if (early) P::issue(a, layer_view(a, 0), prefix_item(a, jp), g, R);
   for (int l = 0; l < a.num_layers; ++l) {
     const LayerView V = layer_view(a, l);
     uint32_t ready = 0;
     for (int k = 0; k < nk; ++k) {
       const PrefixItem it = prefix_item(a, jp + k * a.n_pre_wg);
+      if (k == 0 && !early) {
+        layer_gate(a, it.p, l, ready);
+        P::issue(a, V, it, g, R);
+      }
       P::finish(a, V, it, g, smem, R, [&]() { layer_gate(a, it.p, l, ready); },
                 [&]() {
                   arrive_behind(a, it.p * a.m, a.m, g);
@@ -734,7 +742,7 @@ __device__ __forceinline__ void prefix_loop(const StepArgs& a, int g, int jp, fl
                     P::issue(a, V, prefix_item(a, jp + (k + 1) * a.n_pre_wg), g, R);
                   } else {
                     if (threadIdx.x == 0) peer_mark(a, l, 0);
-                    if (l + 1 < a.num_layers) P::issue(a, layer_view(a, l + 1), prefix_item(a, jp), g, R);
+                    if (early && l + 1 < a.num_layers) P::issue(a, layer_view(a, l + 1), prefix_item(a, jp), g, R);
                   }
                 });
     }

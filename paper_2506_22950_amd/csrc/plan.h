@@ -117,6 +117,8 @@ struct StepArgs {
                                        // wavefront (wavefront w of response work-group i takes item 4i + w).  A per-layer
                                        // launch: 2 with a response (one item) and a merge per wavefront, else 0
   int32_t merge_j0;                    // first merge work-group of a KV head (>= n_pre_wg)
+  int32_t prefix_early;                // 1: a prefix work-group loads its next layer's first chunk behind its
+                                       // arrival, 0: when that layer may start (early_prefix_pays)
   int64_t q_layer_stride, kv_layer_stride, o_layer_stride;
   int64_t prefix_layer_bytes, pool_layer_bytes;
   int32_t* merged;                     // per prompt, kCounterStride apart: merges completed (they only grow);

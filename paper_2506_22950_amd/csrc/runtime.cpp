@@ -903,6 +903,8 @@ infs_status launch_step_layers(infs_ctx* c, const KernelKey& key, StepArgs& a, i
   }
   a.n_suffix_items = roles.n_suffix_items;
   a.resp_cut = cut;
+  a.prefix_early = infs::early_prefix_pays(
+      infs::early_prefix_varies(key.mfma != 0, key.kv8 != 0, key.head_dim, key.prefix_rows), lens, a.S);
   // Merges go opposite the prefix work-groups (index j shares its CU with j + nj/2, see
   // mate_gate), else after the response work-groups.
   a.merge_j0 = (nj % 2 == 0 && a.n_pre_wg <= nj / 2 && a.n_merge_wg <= nj / 2) ? nj / 2 : a.n_pre_wg + a.n_suf_wg;

@@ -202,6 +202,34 @@ inline int most_response_tokens(const StepRoles& r, int S, const int32_t* len, i
   return most;
 }
 
+// Whether the prefix work-groups of a step launch load a layer's first chunk behind
+// the arrival of the layer before (StepArgs::prefix_early) rather than when the layer
+// may start; early_prefix_varies names the shapes where it may be either.  The 32-row
+// tile asks for the most: its two row groups each load the whole 128-token
+// chunk at once (the 16-row tile loads it once, wider tiles two blocks at a time).
+// With long responses, whose partials and merges fill a layer's end, that costs more
+// than it hides.  Loads at the layer's start and behind the arrival, us a step: 28
+// layers, prompt 2048, 16 slots of 2 rows, mean response 140 tokens 270.8 and 264.6,
+// 550 324.9 and 322.1, 750 360.4 and 362.1, 1900 330.8 and 334.4, 3400 319.3 and 330.7;
+// 16 KV heads (12 layers) 140 159.7 and 152.2, 750 284.1 and 284.6, 2400 292.8 and 299.9;
+// prompt 3000 140 149.9 and 144.9, 2400 170.3 and 173.1.  Elsewhere long responses gain
+// too or stay: 64 rows (4 heads per KV head) 2400 194.1 and 185.3, (32 slots) 2700 192.1
+// and 192.2, 3400 159.6 and 151.6; 16 rows (1 head) 3400 145.4 and 146.8, (two prompts)
+// 2400 153.7 and 154.0; E4M3 3400 307.4 and 294.0; head size 64, 32 rows, 3400 124.2 and
+// 121.9; plain rows up to 600 tokens 123.7 and 121.7, 1800 134.8 and 136.4.
+constexpr bool early_prefix_varies(bool mfma, bool kv8, int head_dim, int prefix_rows) {
+  return mfma && !kv8 && head_dim == 128 && prefix_rows == 32;
+}
+constexpr int kEarlyPrefixTokens = 768;
+inline bool early_prefix_pays(bool varies, const int32_t* len, int S) {
+  int64_t tokens = 0, live = 0;
+  for (int s = 0; s < S; ++s) {
+    tokens += len[s];
+    live += len[s] > 0;
+  }
+  return !varies || tokens < live * kEarlyPrefixTokens;
+}
+
 // The split of a step with one response piece per wavefront (bf16 and E4M3
 // pages): the four wavefronts of a response work-group take a piece each, of
 // whichever slots, and hand in a partial each, without a barrier or a combine

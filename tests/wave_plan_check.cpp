@@ -80,6 +80,14 @@ int main() {
       {560, 4, 1024, true}, {2560, 9, 1024, true}, {2208, 5, 512, true}};
   for (int cs = 0; cs < (int)(sizeof shorts / sizeof *shorts); ++cs)
     CHECK(short_responses_pay(shorts[cs].busy, 512, shorts[cs].partials, shorts[cs].outputs) == shorts[cs].pays);
+  // the prefix loads ahead of a layer: all but long responses on the bf16 32-row tile
+  {
+    const int cs = -1;
+    const int32_t shorter[3] = {767, 0, 768}, longer[3] = {768, 0, 768};
+    CHECK(early_prefix_pays(true, shorter, 3) && !early_prefix_pays(true, longer, 3) && early_prefix_pays(false, longer, 3));
+    CHECK(early_prefix_varies(true, false, 128, 32) && !early_prefix_varies(true, true, 128, 32));
+    CHECK(!early_prefix_varies(true, false, 64, 32) && !early_prefix_varies(true, false, 128, 64));
+  }
   std::printf("applied %d failures %d\n", applied, fails);
   return fails || applied < 1000;
 }
