@@ -398,6 +398,8 @@ def summarize_stats(workload, stats_dir, bench_out, entry="decode_step_layers", 
     main = [r for r in rows if kernel in r["Name"]]
     if not main:
         raise SystemExit(f"no {kernel} row in {files[0]}")
+    # the kernel's variants together (one piece per work-group or per wavefront)
+    avg = sum(float(r["TotalDurationNs"]) for r in main) / sum(int(r["Calls"]) for r in main)
     out = [f"# rocprofv3 kernel statistics, workload {workload}: {passes} whole group decodes",
            f"# ({b['warmup']} warmup, {b['steps']} timed, then the HIP-event and the device-clock timing passes)",
            "# of the command below, run on one MI355X from the repository root after: cd /tmp && export TMPDIR=/tmp",
@@ -414,7 +416,7 @@ def summarize_stats(workload, stats_dir, bench_out, entry="decode_step_layers", 
                    f"{float(r['MaxNs']) / 1e3:>10.3f}{float(r['TotalDurationNs']) / 1e6:>11.2f}{float(r['Percentage']):>7.2f}")
     out += ["", f"{kernel} full name: " + main[0]["Name"],
             f"{kernel} launches per group decode: {b['roofline']['launches'] if b.get('roofline') else 'n/a'}; "
-            f"average by the profiler {float(main[0]['AverageNs']) / 1e3:.3f} us, by HIP events in that run "
+            f"average by the profiler {avg / 1e3:.3f} us, by HIP events in that run "
             f"{b['roofline']['avg_launch_us'] if b.get('roofline') else 'n/a'} us"]
     return "\n".join(out)
 

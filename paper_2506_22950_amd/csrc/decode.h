@@ -756,7 +756,7 @@ struct RespMfma {
 // rows at d = 128), by loads in bf16.  The wavefront dot products it replaces
 // spent their time summing across lanes: a 28-layer fp32 step of 8 slots (2
 // rows each, 16 prefix rows, P = 1000) took 1834 us with them at one wavefront
-// per SIMD and takes 496 us with tiles at two; bf16 with 2 rows (8 layers,
+// per SIMD and takes 487 us with tiles at two; bf16 with 2 rows (8 layers,
 // P = 2483) took 213 us and takes 151.  Short chains keep the fp32 error where
 // it was (1.8e-7 against 1.9e-7 relative); one chain of D is 465 us and 2.1e-7.
 // ----------------------------------------------------------------------------
